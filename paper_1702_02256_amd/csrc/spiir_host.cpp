@@ -58,6 +58,7 @@ struct Plan {
     int lc[SPIIR_MAX_BANDS] = {};
     int xcap = 0, copies = 2;
     int nrun_max = 1, npiece_max = 1;
+    int lanes_used = 64;  // most lanes of a workgroup that hold filters, in whole waves
     int lds_filter = 0, lds_stage = 0, lds_up = 0;
     int64_t total_filters = 0, n_slots = 0, zw_elems = 0, ring_total = 0;
     int workspace = SPIIR_WORKSPACE_OWN;
@@ -216,6 +217,7 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
     };
     auto close_wg = [&](int h) {
         if (cur.lanes == 0) return;
+        p.lanes_used = std::max(p.lanes_used, (cur.lanes + 63) & ~63);
         WgDesc w{};
         w.band = h;
         w.slot_base = p.n_slots;
@@ -953,6 +955,32 @@ hipError_t wait_banks(int32_t n_req, const spiir_request* req, hipStream_t s)
 // bank path without a device fault.
 const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 
+// Threads per lane of the pipelined filter kernel for a launch, or 0 for
+// k_filter, which the results do not depend on.  `rounds`: the launch's work in
+// workgroups as long as its longest (its samples over the longest
+// workgroup's), `lanes` the most lanes of a workgroup that hold filters.  The
+// pipelined kernel wins while the compute units are short of waves, k_filter
+// (four waves per SIMD, half the registers) once they are not.  Measured, us
+// per block, k_filter / X = 2 / X = 1 by groups of 256 lanes per compute unit
+// (g): multi-rate banks of 64, 700, 1024, 1400, 2048 templates (g = 0.08, 0.91,
+// 1.33, 1.82, 2.63) 526 / 333 / 393, 548 / 374 / 422, 589 / 530 / 438,
+// 633 / 702 / 545, 711 / 972 / 753; single-rate banks of 64, 512, 768
+// templates of 512 filters (g = 0.12, 1, 1.5) 268 / 159 / 188, 284 / 179 / 207,
+// 321 / 336 / 271; blocks of 512 samples of 512 and 1024 multi-rate templates
+// 78 / 61 / 71 and 86 / 108 / 84.  X = 4 pays where a workgroup is at most 128
+// lanes, so that the four threads still make two waves per SIMD: one
+// template of 128 filters, 4096 samples 586 (k_filter), 143 (X = 4), 203 (X = 2).
+// Runs of fewer than 64 samples (time chunks of 32) lose to the two tiles the
+// pipeline needs to fill, 39 / 44; 512 lanes leave no room for more threads, and
+// X = 1 there gains nothing (530 / 562; 1024 single-rate templates 301 / 303).
+int pipe_threads(int F, int lanes, int longest, double rounds)
+{
+    const double g = rounds * lanes / (256.0 * kComputeUnits);
+    if (F != 4 || 2 * lanes > kPipeThreads || longest < 4 * kTile || g > 2.0) return 0;
+    if (g > 1.0) return 1;
+    return 4 * lanes <= kPipeThreads ? 4 : 2;
+}
+
 // Kernels of one batch on `s`: per inner chunk of at most kInnerBlock base-rate
 // samples, the staging kernel (which advances each bank's device clock), the
 // filter kernel and the upsample-and-add kernel.  Reads no host-side sample
@@ -1071,6 +1099,27 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                     lds = std::max(lds, req[rmap[k]].bank->plan.lds_filter);
             return lds;
         };
+        auto run_filter = [&](const Shape& sh, const LaunchArgs& X, int nblocks, bool local) {
+            const int lds = shape_lds(sh, local);
+            if (sh.engine == SPIIR_ENGINE_MFMA) return launch_filter_mfma(X, nblocks, lds, s);
+            int64_t work = 0;  // samples of all workgroups, and of the longest
+            int longest = 1, lanes = 64;
+            for (int k = 0; k < X.nreq; ++k) {
+                const Plan& p = req[rmap[k]].bank->plan;
+                if (!same(shape_of(k), sh)) continue;
+                lanes = std::max(lanes, p.lanes_used);
+                for (int h = 0; h < p.H; ++h) {
+                    const int nwg = p.band_wg0[h + 1] - p.band_wg0[h], nh = X.req[k].n >> h;
+                    if (nwg == 0) continue;
+                    work += (int64_t)nwg * nh;
+                    longest = std::max(longest, X.req[k].nchunk > 1 ? std::min(nh, p.lc[h]) : nh);
+                }
+            }
+            const int x = pipe_threads(sh.F, lanes, longest, (double)work / longest);
+            if (x) return launch_filter_pipe(x, local, sh.prec, X, nblocks, lanes, lds, s);
+            return local ? launch_filter_local(sh.F, sh.prec, X, nblocks, sh.L, lds, s)
+                         : launch_filter(sh.F, sh.prec, X, nblocks, sh.L, lds, s);
+        };
         mark(0);
         e = (hipError_t)launch_stage(A, lds_s, s);
         mark(1);
@@ -1080,7 +1129,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                 LaunchArgs X = A;
                 const int n1 = segments(X, true, sh);
                 if (e == hipSuccess && n1 > 0)
-                    e = (hipError_t)launch_filter_local(sh.F, sh.prec, X, n1, sh.L, shape_lds(sh, true), s);
+                    e = (hipError_t)run_filter(sh, X, n1, true);
             }
         if (e == hipSuccess && split && nchain > 0) e = (hipError_t)launch_chain(A2, nchain, s);
         for (const Shape* sp = shape_buf; sp != shapes_end; ++sp) {
@@ -1088,9 +1137,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             LaunchArgs X = A;
             const int n0 = segments(X, false, sh);
             if (e == hipSuccess && n0 > 0)
-                e = (hipError_t)(sh.engine == SPIIR_ENGINE_MFMA
-                                     ? launch_filter_mfma(X, n0, shape_lds(sh, false), s)
-                                     : launch_filter(sh.F, sh.prec, X, n0, sh.L, shape_lds(sh, false), s));
+                e = (hipError_t)run_filter(sh, X, n0, false);
         }
         mark(2);
         if (e == hipSuccess) e = (hipError_t)launch_upadd(A, ntm, lds_u, s);

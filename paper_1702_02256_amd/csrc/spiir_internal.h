@@ -36,6 +36,8 @@ constexpr size_t kScratchBytes = (size_t)SPIIR_NOALLOC_MAX_WORKSPACE;
 // Largest workgroup of the filter kernel for F filters per lane: with 8
 // filters a lane needs more than 128 VGPRs, so at most 2 waves per SIMD.
 constexpr int filter_max_threads(int F) { return F >= 8 ? 512 : 1024; }
+// Largest workgroup of the pipelined filter kernel (256 VGPRs a lane).
+constexpr int kPipeThreads = 512;
 // Waves per SIMD the compiler must leave room for (caps VGPRs at 512 / n):
 // with 4 filters and the plain sum a lane fits in 96 VGPRs (spills only
 // outside the sample loop), so 5 waves; the compensated sum needs more, so 4.
@@ -169,6 +171,10 @@ int launch_prep(const c64* a, const c64* b, int64_t n, int C, c32* fa, c32* fb, 
                 const int32_t* slot_lc, c32* fal, void* stream);
 int launch_filter_local(int F, int precision, const LaunchArgs& a, int nblocks, int L, int lds_bytes,
                         void* stream);
+// F = 4 only: the pipelined filter kernel with X threads per lane, X in {1, 2, 4}
+// (its end-state pass with `local`).
+int launch_filter_pipe(int X, bool local, int precision, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
+                       void* stream);
 int launch_chain(const LaunchArgs& a, int64_t nblocks, void* stream);
 int launch_fill(void* p, int64_t bytes, void* stream);
 int filter_max_lds();

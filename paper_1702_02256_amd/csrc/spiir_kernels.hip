@@ -587,6 +587,534 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 }
 
 // ---------------------------------------------------------------------------
+// The filter bank for launches that do not fill the device: k_filter's layout,
+// arithmetic and order of every sum (so its outputs and states bit for bit),
+// with the wait for each cross-lane step hidden and, with X > 1, X threads per
+// lane of the layout.
+//
+// What bounds k_filter there is latency: with one or two waves per SIMD a tile
+// of 16 samples spends more time waiting for the LDS (64 clocks a read), the
+// two reduction levels and the barrier between them than issuing.  Here one
+// iteration runs three tiles at once: the recurrences of tile k, level 1 of
+// tile k - 1 and level 2 of tile k - 2, with the reduction levels' reads
+// issued before the recurrences and each x pair read one tile ahead into the
+// registers its predecessor leaves, so no step waits and one barrier per tile
+// is left.
+//
+// A lone wave issues at most one instruction per 4.4 clocks (measured), and
+// more waves add to that.  So a launch with few waves splits every lane's F
+// filters over X neighbouring threads: the in-lane pairwise tree becomes DPP
+// additions in the same order.  Threads with odd p hold the swapped form of
+// the state their slot stores (see one_step), so that each DPP addition
+// serves both components.
+//
+// Measured, us per launch, k_filter -> this kernel: 1 template of 128 filters,
+// 4096 samples 586 -> 143 (X = 4; 0.53 us per tile where k_filter takes 2.3);
+// 512 multi-rate templates, 4096 samples 534 -> 375 (X = 2); 1024 of them
+// 575 -> 427 (X = 1); 160 of them, 576 samples 88 -> 61 (X = 2).
+//
+// At most kPipeThreads threads, so that a lane may hold 256 registers: a spilled
+// register would be read back behind the workspace stores, a microsecond.
+// ---------------------------------------------------------------------------
+template <int CTRL>
+__device__ __forceinline__ float dpp_mov(float v)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xF, 0xF, true));
+}
+
+// The pair sum of one sample from the threads' F/X filters, one component in
+// each thread: the real one where lane and part are both even or both odd.
+template <int X, int NF>
+__device__ __forceinline__ float split_sum(float (&tr)[NF], float (&ti)[NF])
+{
+    lane_sum<NF>(tr, ti);
+    float s = tr[0] + dpp_mov<0xB1>(ti[0]);      // quad_perm [1,0,3,2]
+    if (X == 2) s += dpp_mov<0x1B>(s);           // quad_perm [3,2,1,0]
+    if (X == 4) {
+        s += dpp_mov<0x4E>(s);                   // quad_perm [2,3,0,1]
+        s += dpp_mov<0x141>(s);                  // row_half_mirror
+    }
+    return s;
+}
+
+// Two samples of Eq. 7 (see one_step) with the pair sums returned.
+template <int X, int NF, bool SUM>
+__device__ __forceinline__ void split_step(const float (&xv)[NF], float& out, const float (&ar)[NF],
+                                           const float (&ai)[NF], const float (&br)[NF],
+                                           const float (&bi)[NF], float (&yr)[NF], float (&yi)[NF])
+{
+    float tr[NF], ti[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const float pr = br[f] * xv[f], pi = bi[f] * xv[f];
+        const float nr = fmaf(ar[f], yr[f], fmaf(-ai[f], yi[f], pr));
+        const float ni = fmaf(ar[f], yi[f], fmaf(ai[f], yr[f], pi));
+        yr[f] = nr; yi[f] = ni;
+        tr[f] = nr; ti[f] = ni;
+    }
+    if (SUM) out = split_sum<X, NF>(tr, ti);
+}
+
+// Waits for the wave's global loads (vmcnt 0).  A load whose wait the compiler
+// cannot place on every path costs a wait in the loop that follows, and there
+// it would also wait for the workspace stores, a microsecond each tile.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// The same for LDS reads (lgkmcnt 0).
+__device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
+
+// Keeps the LDS read before it from being fused with the next one (see
+// tile_full), while arithmetic may still move across.
+__device__ __forceinline__ void keep_single() { __builtin_amdgcn_sched_barrier(0x6); }
+
+constexpr int kAhead = 4;     // x pairs read ahead
+constexpr int kRunAhead = 8;  // run sums a level-2 task reads ahead
+
+
+template <int F, int X, bool COMP, bool LOCAL>
+__global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
+{
+    constexpr int NF = F / X;
+    constexpr int kPairs = kRunLanes / 2;
+    using Acc = typename std::conditional<COMP, double, float>::type;
+    extern __shared__ float sm[];
+    const int bid = blockIdx.x;
+    int lo = 0, hi = args.nseg;
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (args.cum[mid] <= bid) lo = mid;
+        else hi = mid;
+    }
+    const ReqArg& q = args.req[args.seg_req[lo]];
+    const int h = args.seg_band[lo];
+    CBankDev* bd = cmem(q.bd);
+    const int nwg_h = bd->band_wg0[h + 1] - bd->band_wg0[h];
+    const int li = bid - args.cum[lo];
+    const int tc = li / nwg_h;
+    const WgDesc wg = cmem(bd->wg)[bd->band_wg0[h] + (li - tc * nwg_h)];
+    const int NT = blockDim.x, L = bd->L;  // lanes beyond NT / X are padding
+    const int tid = threadIdx.x;
+    const int ln = tid / X, part = tid % X;  // lane of the layout, thread of the lane
+    const bool flip = part & 1;
+    const int nh = q.n >> h;
+    const int64_t s0h = cmem(bd->clock)[0] >> h;
+    const Chunk ch = chunk_range(tc, q.nchunk, s0h, nh, bd->lc[h]);
+    if (ch.k0 >= ch.k1 || (LOCAL && ch.last)) return;  // whole workgroup
+    const int64_t cmask = bd->C - 1;
+    const int nrun = bd->nrun_max;
+
+    // the LDS layout of k_filter
+    const bool two_copies = bd->copies == 2;
+    float* E0 = sm;
+    float* E1 = sm + bd->xcap;
+    c32* pbuf = reinterpret_cast<c32*>(sm + bd->copies * bd->xcap);
+    c32* l2buf = pbuf + (L / 2) * (kTile + 1);
+    long long* pzoff = reinterpret_cast<long long*>(l2buf + 2 * kTile * nrun);
+    int* lmeta = reinterpret_cast<int*>(pzoff + bd->npiece_max);
+    int2* prun = reinterpret_cast<int2*>(lmeta + L);
+
+    for (int i = tid; i < L; i += NT) lmeta[i] = cmem(bd->lane_meta)[wg.meta_base + i];
+    for (int p = tid; p < wg.npiece; p += NT) {
+        const PieceDesc pd = cmem(bd->piece)[wg.piece_base + p];
+        pzoff[p] = pd.zoff;
+        prun[p] = make_int2(pd.run0, pd.run1);
+    }
+    for (int i = tid; i < 2 * kTile * nrun; i += NT) l2buf[i] = c32{0.0f, 0.0f};
+
+    float ar[NF], ai[NF], br[NF], bi[NF], dr[NF], di[NF], yr[NF], yi[NF], ur[NF], ui[NF];
+    int dl[NF];
+    const c32* ysrc = bd->y;  // start states: as in k_filter
+    const c32* yssrc = bd->ys;
+    if (!ch.first) ysrc = yssrc = bd->schain + (int64_t)tc * bd->n_slots;
+    else if (!LOCAL && !ch.last) {
+        ysrc = bd->schain + (int64_t)tc * bd->n_slots;
+        yssrc = bd->ys0;
+    }
+    const SPIIR_AS_GLOBAL c32* ysg = gmem(ysrc);
+    const SPIIR_AS_GLOBAL c32* yssg = gmem(yssrc);
+    const int64_t slot0_ = wg.slot_base + (int64_t)part * NF * L + ln;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const int64_t g = slot0_ + (int64_t)f * L;
+        c32 y = ysg[g], ys = yssg[g];
+        if (LOCAL && !ch.first) y = ys = c32{0.0f, 0.0f};
+        if (LOCAL && ch.first) {
+            gmem(bd->schain)[(int64_t)tc * bd->n_slots + g] = y;
+            gmem(bd->ys0)[g] = ys;
+        }
+        c32 a = cmem(bd->a)[g], b = cmem(bd->b)[g], d = cmem(bd->dc)[g];
+        if (flip) {
+            a.y = -a.y;
+            d.y = -d.y;
+            b = c32{b.y, b.x};
+            y = c32{y.y, y.x};
+            ys = c32{ys.y, ys.x};
+        }
+        ar[f] = a.x; ai[f] = a.y;
+        br[f] = b.x; bi[f] = b.y;
+        dr[f] = d.x; di[f] = d.y;
+        yr[f] = y.x; yi[f] = y.y;
+        if (ch.first) {
+            ur[f] = ys.x; ui[f] = ys.y;
+        } else {
+            ur[f] = fmaf(d.x, y.x, -d.y * y.y);
+            ui[f] = fmaf(d.x, y.y, d.y * y.x);
+        }
+        dl[f] = cmem(bd->off)[g];
+    }
+    __syncthreads();
+
+    // Level-1 role: sample row j1 of the 16-lane group q1 (the wave's own
+    // 4 / X groups); with X > 1 a thread sums one component, c1 (with X = 4 the
+    // upper half-wave repeats the lower's sums).
+    constexpr int kGroups = 4 / X;  // 16-lane groups per wave
+    const int wl = tid & 63;
+    const int j1 = wl & (kTile - 1);
+    const int q1 = X == 1 ? (tid >> 6) * 4 + (((wl >> 4) & 1) << 1) + (wl >> 5)
+                          : (tid >> 6) * kGroups + ((wl >> 4) & (kGroups - 1));
+    const int c1 = X == 1 ? 0 : ((wl >> 4) / kGroups) & 1;
+    unsigned endmask = 0;
+    int slot0 = -1;
+    // k_filter's vote: the tree only where all four groups of 64 lanes are single runs
+    bool single = true;
+#pragma unroll
+    for (int i = 0; i < kPairs; ++i) {
+        const int sl = lmeta[q1 * kRunLanes + 2 * i + 1] & 0xffff;
+        if (sl != kSlotNone) {
+            endmask |= 1u << i;
+            if (slot0 < 0) slot0 = sl;
+        }
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            const int sg = lmeta[((q1 & ~3) + g) * kRunLanes + 2 * i + 1] & 0xffff;
+            single &= (sg != kSlotNone) == (i == kPairs - 1);
+        }
+    }
+    const bool wave_single_run = __all(single);
+    const float* grp = reinterpret_cast<const float*>(pbuf + q1 * kPairs * (kTile + 1) + j1) + c1;
+
+    // Level-2 role: row j2 of piece p2 (with X > 1, one component, c2), for the
+    // waves that hold such tasks; tasks beyond NT are summed in a loop.
+    constexpr int kComp = X == 1 ? 1 : 2;  // tasks per (piece, row)
+    const int ntask2 = wg.npiece * kTile * kComp;
+    // The last waves take them: they are the ones that may be idle.
+    const int t2 = NT - 64 - (tid & ~63) + wl;
+    const bool duty = __builtin_amdgcn_readfirstlane(t2 & ~63) < ntask2;
+    const bool more_tasks = ntask2 > NT;
+    const int j2 = (t2 / kComp) & (kTile - 1), c2 = X == 1 ? 0 : t2 & 1;
+    const int p2 = min(t2 / (kComp * kTile), wg.npiece - 1);
+    const int run0 = prun[p2].x, run1 = prun[p2].y;
+    const bool long_run = __any(run1 - run0 > kRunAhead);
+    SPIIR_AS_GLOBAL float* zrow = reinterpret_cast<SPIIR_AS_GLOBAL float*>(gmem(q.zw) + pzoff[p2] + j2) + c2;
+    const int l2off = 2 * (j2 * nrun + run0) + c2;
+
+    const int S = bd->S[h];
+    const SPIIR_AS_CONST float* ring = cmem(bd->rings) + bd->ring_off[h];
+    const int64_t mk = bd->ring_mask[h];
+    // Where the thread stores pair sums: of the X threads that hold the same
+    // component of a pair, thread px stores every X-th sample.
+    const int px = X == 1 ? 0 : X == 2 ? part : 2 * (ln & 1) + (part >> 1);
+    float* pcol = reinterpret_cast<float*>(pbuf + (ln >> 1) * (kTile + 1)) + ((ln ^ part) & 1);
+    float* const l2f = reinterpret_cast<float*>(l2buf);
+    const int l2size = 2 * kTile * nrun;  // floats of one run-sum buffer
+
+    // A wave whose lanes hold no filter and no state (padding) adds exact
+    // zeros, as the run-sum buffers hold from the start: it takes no part in
+    // the tiles but their barriers and its level-2 tasks.
+    bool zero = true;
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+        zero &= ar[f] == 0.0f && ai[f] == 0.0f && br[f] == 0.0f && bi[f] == 0.0f && yr[f] == 0.0f && yi[f] == 0.0f &&
+                ur[f] == 0.0f && ui[f] == 0.0f;
+    const bool idle = __all(zero);
+
+    // the tiles in flight: first sample and length of the tile whose partial
+    // sums are in pbuf (1) and of the one whose run sums are in l2buf (2)
+    int k1 = 0, cnt1 = 0, k2 = 0, cnt2 = 0, parity = 0;
+    f32x2_t xv[NF][kAhead];  // the next kAhead x pairs of each filter
+
+    // The reads of both levels, ahead of their use.  Reads past a piece's last
+    // run stay inside the LDS (the piece tables follow the run sums) and are
+    // not used.
+    f32x2_t v1[kPairs], v2[kRunAhead];
+    auto load1 = [&]() {
+#pragma unroll
+        for (int i = 0; i < kPairs; ++i) {
+            const float* p = grp + 2 * i * (kTile + 1);
+            if (X == 1) v1[i] = *reinterpret_cast<const f32x2_t*>(p);
+            else v1[i].x = *p;
+            keep_single();
+        }
+    };
+    auto load2 = [&]() {
+        const float* row = l2f + (parity ^ 1) * l2size + l2off;
+#pragma unroll
+        for (int i = 0; i < kRunAhead; ++i) {
+            const float* p = row + 2 * i;
+            if (X == 1) v2[i] = *reinterpret_cast<const f32x2_t*>(p);
+            else v2[i].x = *p;
+            keep_single();
+        }
+    };
+    // level 1: the run sums of a 16-lane group, in k_filter's two orders.  In
+    // the segmented one every pair stores its running sum in the slot of the
+    // run it belongs to, so the run's last one stays.
+    auto level1 = [&](auto single_run) {
+        float* o = l2f + parity * l2size + 2 * j1 * nrun + c1;
+        auto put = [&](int slot, Acc r, Acc i) {
+            if (X == 1) *reinterpret_cast<f32x2_t*>(o + 2 * slot) = f32x2_t{(float)r, (float)i};
+            else o[2 * slot] = (float)r;
+        };
+        if (single_run.value) {
+            Acc tr[kPairs], ti[kPairs];
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) {
+                tr[i] = v1[i].x;
+                if (X == 1) ti[i] = v1[i].y;
+            }
+#pragma unroll
+            for (int st = 1; st < kPairs; st *= 2)
+#pragma unroll
+                for (int i = 0; i + st < kPairs; i += 2 * st) {
+                    tr[i] += tr[i + st];
+                    if (X == 1) ti[i] += ti[i + st];
+                }
+            put(slot0, tr[0], ti[0]);
+        } else {
+            Acc accr = v1[0].x, acci = X == 1 ? v1[0].y : 0.0f;
+#pragma unroll
+            for (int i = 0; i < kPairs; ++i) {
+                if (i > 0) {
+                    const Acc keep = (Acc)(((endmask >> (i - 1)) & 1u) ^ 1u);
+                    accr = acc_fma(accr, keep, (Acc)v1[i].x);
+                    if (X == 1) acci = acc_fma(acci, keep, (Acc)v1[i].y);
+                }
+                put(slot0 + __popc(endmask & ((1u << i) - 1)), accr, acci);
+            }
+        }
+    };
+    // level 2: a piece's runs in order; the first kRunAhead were read ahead
+    auto level2 = [&]() {
+        Acc accr = 0, acci = 0;
+#pragma unroll
+        for (int i = 0; i < kRunAhead; ++i) {
+            const bool in = run0 + i < run1;
+            accr += in ? (Acc)v2[i].x : (Acc)0;
+            if (X == 1) acci += in ? (Acc)v2[i].y : (Acc)0;
+        }
+        const float* l2r = l2f + (parity ^ 1) * l2size;
+        if (long_run)
+            for (int s = run0 + kRunAhead; s < run1; ++s) {
+                const float* p = l2r + l2off + 2 * (s - run0);
+                accr += p[0];
+                if (X == 1) acci += p[1];
+            }
+        if (t2 < ntask2 && j2 < cnt2) {
+            SPIIR_AS_GLOBAL float* zp = zrow + 2 * k2;
+            if (X == 1) *reinterpret_cast<SPIIR_AS_GLOBAL f32x2_t*>(zp) = f32x2_t{(float)accr, (float)acci};
+            else *zp = (float)accr;
+        }
+        if (more_tasks)
+            for (int task = t2 + NT; task < ntask2; task += NT) {
+                const int p = task / (kComp * kTile), j = (task / kComp) & (kTile - 1), c = task & (kComp - 1);
+                if (j >= cnt2) continue;
+                const int2 rr = prun[p];
+                Acc sr = 0, si = 0;
+                for (int s = rr.x; s < rr.y; ++s) {
+                    const float* v = l2r + 2 * (j * nrun + s) + c;
+                    sr += v[0];
+                    if (X == 1) si += v[1];
+                }
+                SPIIR_AS_GLOBAL float* zp = reinterpret_cast<SPIIR_AS_GLOBAL float*>(gmem(q.zw) + pzoff[p] + k2 + j) + c;
+                zp[0] = (float)sr;
+                if (X == 1) zp[1] = (float)si;
+            }
+    };
+    auto correct = [&](int64_t kend) {  // the carry correction, as in k_filter
+        if ((kend & cmask) != 0) return;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            yr[f] += ur[f];
+            yi[f] += ui[f];
+            ur[f] = fmaf(dr[f], yr[f], -di[f] * yi[f]);
+            ui[f] = fmaf(dr[f], yi[f], di[f] * yr[f]);
+        }
+    };
+    // the pipeline one step on, after tile (k, cnt)
+    auto advance = [&](int k, int cnt) {
+        __syncthreads();
+        k2 = k1; cnt2 = cnt1;
+        k1 = k; cnt1 = cnt;
+        parity ^= 1;
+    };
+    // levels 1 and 2 alone: idle waves, and the end of the block
+    auto levels = [&]() {
+        if (!idle) {
+            load1();
+            if (wave_single_run) level1(std::true_type{});
+            else level1(std::false_type{});
+        }
+        if (duty) {
+            load2();
+            level2();
+        }
+    };
+
+    for (int kb = ch.k0; kb < ch.k1; kb += S) {
+        const int sub = min(S, ch.k1 - kb);
+        const int64_t origin = ((s0h + kb - wg.maxd - 1) >> 6) << 6;
+        const int wn = (int)(s0h + kb + sub - origin);
+        __syncthreads();
+        for (int i0 = tid; i0 <= wn; i0 += kStageBatch * NT) {
+            float v[kStageBatch];
+#pragma unroll
+            for (int u = 0; u < kStageBatch; ++u) {
+                const int i = i0 + u * NT;
+                v[u] = i <= wn ? ring[(origin + i) & mk] : 0.0f;
+            }
+#pragma unroll
+            for (int u = 0; u < kStageBatch; ++u) {
+                const int i = i0 + u * NT;
+                if (i < wn) E0[i] = v[u];
+                if (two_copies && i > 0 && i <= wn) E1[i - 1] = v[u];
+            }
+        }
+        wait_loads();
+        __syncthreads();
+
+        // the run of full tiles [ka, ke) of this window, between partial ones
+        const int ka = min(kb + (int)(-(s0h + kb) & (kTile - 1)), kb + sub);
+        const int ke = max(ka, kb + sub - (int)((s0h + kb + sub) & (kTile - 1)));
+        const int rel0 = (int)(s0h - origin);  // window position of block sample 0
+
+        auto partial = [&](int k, int cnt) {
+            if (cnt <= 0) return;
+            if (!LOCAL) levels();
+            if (!idle) {
+#pragma unroll 1
+                for (int j = 0; j < cnt; ++j) {
+                    float xs[NF], o = 0.0f;
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) xs[f] = E0[rel0 + k + j - dl[f]];
+                    split_step<X, NF, !LOCAL>(xs, o, ar, ai, br, bi, yr, yi);
+                    if (!LOCAL && (j & (X - 1)) == px) pcol[2 * j] = o;
+                }
+                correct(s0h + k + cnt);
+            }
+            if (!LOCAL) advance(k, cnt);
+        };
+        auto full = [&](auto two, auto single_run) {
+            const float* x1[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const int par = two.value ? dl[f] & 1 : 0;
+                x1[f] = (par ? E1 : E0) + (rel0 + ka - dl[f] - par);
+            }
+            auto load_x = [&](int jj, int off) {  // pair jj, off samples on
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    const float* p = x1[f] + off;
+                    if (two.value) xv[f][jj % kAhead] = reinterpret_cast<const f32x2_t*>(p)[jj];
+                    else xv[f][jj % kAhead] = f32x2_t{p[2 * jj], p[2 * jj + 1]};
+                }
+                keep_single();
+            };
+#pragma unroll
+            for (int jj = 0; jj < kAhead; ++jj) load_x(jj, 0);
+            wait_lds();
+#pragma unroll 1
+            for (int k = ka; k < ke; k += kTile) {
+                if (!LOCAL) {
+                    load1();
+                    if (duty) load2();
+                }
+                // the next tile's first pairs (after the last tile its own
+                // again, which are in bounds)
+                const int at = k + kTile < ke ? kTile : 0;
+                float out[kTile];
+#pragma unroll
+                for (int jj = 0; jj < kTile / 2; ++jj) {
+                    float xa[NF], xb[NF];
+#pragma unroll
+                    for (int f = 0; f < NF; ++f) {
+                        xa[f] = xv[f][jj % kAhead].x;
+                        xb[f] = xv[f][jj % kAhead].y;
+                    }
+                    split_step<X, NF, !LOCAL>(xa, out[2 * jj], ar, ai, br, bi, yr, yi);
+                    split_step<X, NF, !LOCAL>(xb, out[2 * jj + 1], ar, ai, br, bi, yr, yi);
+                    if (!LOCAL) {  // after load1
+                        if (X == 1) {
+                            pcol[4 * jj] = out[2 * jj];
+                            pcol[4 * jj + 2] = out[2 * jj + 1];
+                        } else if (X == 2) {
+                            pcol[4 * jj + 2 * px] = px ? out[2 * jj + 1] : out[2 * jj];
+                        } else if (jj & 1) {
+                            const float lo2 = px & 1 ? out[2 * jj - 1] : out[2 * jj - 2];
+                            const float hi2 = px & 1 ? out[2 * jj + 1] : out[2 * jj];
+                            pcol[4 * jj - 4 + 2 * px] = px & 2 ? hi2 : lo2;
+                        }
+                    }
+                    if (jj < kTile / 2 - kAhead) load_x(jj + kAhead, 0);
+                    else load_x(jj - (kTile / 2 - kAhead), at);
+                }
+#pragma unroll
+                for (int f = 0; f < NF; ++f) x1[f] += at;
+                if (!LOCAL) {
+                    level1(single_run);
+                    if (duty) level2();
+                }
+                correct(s0h + k + kTile);
+                if (!LOCAL) advance(k, kTile);
+            }
+        };
+
+        partial(kb, ka - kb);
+        if (idle) {
+            if (!LOCAL)
+                for (int k = ka; k < ke; k += kTile) {
+                    levels();
+                    advance(k, kTile);
+                }
+        } else if (two_copies) {
+            if (LOCAL || wave_single_run) full(std::true_type{}, std::true_type{});
+            else full(std::true_type{}, std::bool_constant<LOCAL>{});
+        } else {
+            if (LOCAL || wave_single_run) full(std::false_type{}, std::true_type{});
+            else full(std::false_type{}, std::bool_constant<LOCAL>{});
+        }
+        partial(ke, kb + sub - ke);
+    }
+    if (!LOCAL) {
+        // the two tiles still in flight
+        for (int i = 0; i < 2; ++i) {
+            levels();
+            advance(0, 0);
+        }
+    }
+
+    auto unflip = [&](float r, float i) { return flip ? c32{i, r} : c32{r, i}; };
+    if (LOCAL) {
+        SPIIR_AS_GLOBAL c32* ue = gmem(bd->uend) + (int64_t)tc * bd->n_slots;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) ue[slot0_ + (int64_t)f * L] = unflip(yr[f], yi[f]);
+        return;
+    }
+    if (!ch.last) return;  // only the block's last chunk carries its state on
+    bool bad = false;
+#pragma unroll
+    for (int f = 0; f < NF; ++f) {
+        const int64_t g = slot0_ + (int64_t)f * L;
+        gmem(bd->y)[g] = unflip(yr[f], yi[f]);
+        gmem(bd->ys)[g] = unflip(ur[f], ui[f]);
+        bad |= !(isfinite(yr[f]) && isfinite(yi[f]));
+    }
+    if (bad) {
+        const int p = lmeta[ln] >> 16;
+        atomicOr(&bd->flags[cmem(bd->piece)[wg.piece_base + p].tmpl], 1);
+    }
+}
+
+// ---------------------------------------------------------------------------
 // The filter bank on the matrix cores (single-rate banks; engine MFMA).
 //
 // Over a chunk of T = 8 samples starting at an absolute multiple of 8 (c is
@@ -1265,6 +1793,16 @@ static int allow_lds_t()
     return e;
 }
 
+template <int X>
+static int allow_pipe_lds_t()
+{
+    int e = 0;
+    for (const void* k : {(const void*)k_filter_pipe<4, X, false, false>, (const void*)k_filter_pipe<4, X, true, false>,
+                          (const void*)k_filter_pipe<4, X, false, true>})
+        if (!e) e = (int)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, filter_max_lds());
+    return e;
+}
+
 // Raises the dynamic LDS limit of the filter-kernel variants and the
 // upsample-and-add kernel on the current device (done outside any launch
 // sequence, so recorded sequences hold launches only).
@@ -1275,6 +1813,9 @@ int allow_filter_lds()
     if (!e)
         e = (int)hipFuncSetAttribute((const void*)k_filter_mfma, hipFuncAttributeMaxDynamicSharedMemorySize,
                                      filter_max_lds());
+    if (!e) e = allow_pipe_lds_t<1>();
+    if (!e) e = allow_pipe_lds_t<2>();
+    if (!e) e = allow_pipe_lds_t<4>();
     if (!e) e = allow_lds_t<1, false>();
     if (!e) e = allow_lds_t<1, true>();
     if (!e) e = allow_lds_t<2, false>();
@@ -1320,6 +1861,30 @@ int launch_filter_local(int F, int precision, const LaunchArgs& a, int nblocks, 
 {
     (void)precision;
     return launch_filter_any<true>(F, SPIIR_FP32, a, nblocks, L, lds_bytes, (hipStream_t)stream);
+}
+
+template <int X, bool LOCAL>
+static int launch_pipe_t(bool comp, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes, hipStream_t s)
+{
+    if (comp && !LOCAL)
+        hipLaunchKernelGGL((k_filter_pipe<4, X, !LOCAL, LOCAL>), dim3(nblocks), dim3(lanes * X), lds_bytes, s, a);
+    else
+        hipLaunchKernelGGL((k_filter_pipe<4, X, false, LOCAL>), dim3(nblocks), dim3(lanes * X), lds_bytes, s, a);
+    return (int)hipGetLastError();
+}
+
+int launch_filter_pipe(int X, bool local, int precision, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
+                       void* stream)
+{
+    const bool comp = !local && precision == SPIIR_FP32_COMPENSATED;
+    hipStream_t s = (hipStream_t)stream;
+    if (local)
+        return X == 1 ? launch_pipe_t<1, true>(comp, a, nblocks, lanes, lds_bytes, s)
+             : X == 2 ? launch_pipe_t<2, true>(comp, a, nblocks, lanes, lds_bytes, s)
+                      : launch_pipe_t<4, true>(comp, a, nblocks, lanes, lds_bytes, s);
+    return X == 1 ? launch_pipe_t<1, false>(comp, a, nblocks, lanes, lds_bytes, s)
+         : X == 2 ? launch_pipe_t<2, false>(comp, a, nblocks, lanes, lds_bytes, s)
+                  : launch_pipe_t<4, false>(comp, a, nblocks, lanes, lds_bytes, s);
 }
 
 int launch_filter_mfma(const LaunchArgs& a, int nblocks, int lds_bytes, void* stream)
