@@ -38,11 +38,11 @@ constexpr size_t kScratchBytes = (size_t)SPIIR_NOALLOC_MAX_WORKSPACE;
 constexpr int filter_max_threads(int F) { return F >= 8 ? 512 : 1024; }
 // Largest workgroup of the pipelined filter kernel (256 VGPRs a lane).
 constexpr int kPipeThreads = 512;
-// Waves per SIMD the compiler must leave room for (caps VGPRs at 512 / n):
-// with 4 filters and the plain sum a lane fits in 96 VGPRs (spills only
-// outside the sample loop), so 5 waves; the compensated sum needs more, so 4.
-// With 6 filters, 4 (128 VGPRs; again no spills in the sample loop).
-constexpr int filter_min_waves(int F, bool comp) { return F == 4 ? (comp ? 4 : 5) : F == 6 ? 4 : 1; }
+// Waves per SIMD the compiler must leave room for (caps VGPRs at 512 / n): with 4
+// and 6 filters a lane 4 waves, 128 VGPRs.  (With 4 filters and the plain sum
+// the kernel also fits 96, 5 waves, but spills ten; LDS keeps the banks that
+// fill the device at 4 waves or fewer anyway.)
+constexpr int filter_min_waves(int F, bool comp) { return F == 4 || F == 6 ? 4 : 1; }
 
 struct alignas(8) c32 {
     float x, y;
