@@ -58,6 +58,7 @@ struct Plan {
     int lc[SPIIR_MAX_BANDS] = {};
     int xcap = 0, copies = 2;
     int nrun_max = 1, npiece_max = 1;
+    bool whole_templates = true;  // every segment is one piece
     int lanes_used = 64;  // most lanes of a workgroup that hold filters, in whole waves
     int lds_filter = 0, lds_stage = 0, lds_up = 0;
     int64_t total_filters = 0, n_slots = 0, zw_elems = 0, ring_total = 0;
@@ -297,7 +298,10 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
         const int64_t zstride = p.zstride[h];
         for (int t = 0; t < T; ++t) {
             const int M = d->n_filters[t * H + h];
-            if (M == 0) continue;
+            if (M == 0) {
+                p.whole_templates = false;
+                continue;
+            }
             // an even number of lanes: lane pairs never straddle a run boundary
             const int nl = (((M + F - 1) / F) + 1) & ~1;
             const int64_t base = moff[t * H + h];
@@ -422,6 +426,8 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
                 placed += take;
             }
             cur_counts = counts[wg_seen];
+            if (sg.npiece == 1) p.piece.back().whole = 1;
+            else p.whole_templates = false;
         }
         close_wg(h);
         cur_counts = fresh_counts();
@@ -450,7 +456,7 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
     fp += (size_t)p.ring_total * sizeof(float) + (size_t)(p.td + p.tu) * sizeof(float);
     if (p.workspace == SPIIR_WORKSPACE_OWN) fp += (size_t)p.zw_elems * sizeof(c32);
     fp += (size_t)T * H * p.hu_len * sizeof(c32) + (size_t)T * sizeof(int32_t) + sizeof(BankDev);
-    fp += 2 * sizeof(int64_t);
+    fp += 3 * sizeof(int64_t);
     if (p.P > 1)  // a1^lc, end states, chained states, entering chunk-start state, exponents
         fp += (size_t)p.n_slots * sizeof(c32) * (1 + 2 * (size_t)(p.P + 1) + 1);
     p.footprint = fp;
@@ -743,7 +749,7 @@ int make_plan_mfma(const spiir_bank_desc* d, Plan& p)
     fp += (size_t)p.ring_total * sizeof(float) + (size_t)(p.td + p.tu) * sizeof(float);
     if (p.workspace == SPIIR_WORKSPACE_OWN) fp += (size_t)p.zw_elems * sizeof(c32);
     fp += (size_t)T * p.hu_len * sizeof(c32) + (size_t)T * sizeof(int32_t) + sizeof(BankDev);
-    fp += 2 * sizeof(int64_t);
+    fp += 3 * sizeof(int64_t);
     p.footprint = fp;
     p.n_groups = (int32_t)p.wg.size();
     p.n_pieces = (int32_t)p.piece.size();
@@ -867,7 +873,7 @@ int zero_state(spiir_bank* b, hipStream_t s)
     e |= launch_fill(b->rings, p.ring_total * (int64_t)sizeof(float), s);
     e |= launch_fill(b->uphist, (int64_t)p.T * p.H * p.hu_len * (int64_t)sizeof(c32), s);
     e |= launch_fill(b->flags, (int64_t)p.T * (int64_t)sizeof(int32_t), s);
-    e |= launch_fill(b->clock, 2 * (int64_t)sizeof(int64_t), s);
+    e |= launch_fill(b->clock, 3 * (int64_t)sizeof(int64_t), s);
     return e;
 }
 
@@ -996,6 +1002,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         std::memset(&A, 0, sizeof(A));
         int rmap[SPIIR_MAX_BATCH];
         int lds_s = 0, lds_u = 0, ntm = 0, maxH = 0;
+        bool need_stage = false;
         for (int r = 0; r < n_req; ++r) {
             const spiir_request& q = req[r];
             if (q.n <= c0) continue;
@@ -1015,6 +1022,15 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             ra.c0 = (int32_t)c0;
             ra.thr2 = thr2;
             ra.nchunk = p.P > 1 ? p.P + 1 : 1;
+            // a single-rate bank needs neither the cascade nor, where every
+            // template is one piece and z is wanted, the upsample-and-add pass
+            // (time chunks of a few tiles gain nothing from it: each of their
+            // workgroups would wait for the clock)
+            ra.direct = p.H == 1 && p.engine == SPIIR_ENGINE_VALU && p.n_groups > 0 && p.P == 1;
+            ra.nblocks = p.n_groups;
+            ra.z_direct = ra.direct && ra.z && !ra.peaks;
+            ra.T = ra.z_direct && p.whole_templates ? 0 : p.T;
+            need_stage |= !ra.direct;
             lds_s = std::max(lds_s, p.lds_stage);
             lds_u = std::max(lds_u, p.lds_up);
             maxH = std::max(maxH, p.H);
@@ -1079,8 +1095,8 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         }
         A.tcum[0] = 0;
         for (int k = 0; k < A.nreq; ++k) {
-            A.tcum[k + 1] = A.tcum[k] + req[rmap[k]].bank->plan.T;
-            ntm += req[rmap[k]].bank->plan.T;
+            A.tcum[k + 1] = A.tcum[k] + A.req[k].T;
+            ntm += A.req[k].T;
         }
 
         // kernel timing: kind 0 staging, kind 1 the filter bank (with the
@@ -1121,7 +1137,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                          : launch_filter(sh.F, sh.prec, X, nblocks, sh.L, lds, s);
         };
         mark(0);
-        e = (hipError_t)launch_stage(A, lds_s, s);
+        if (need_stage) e = (hipError_t)launch_stage(A, lds_s, s);
         mark(1);
         if (split)
             for (const Shape* sp = shape_buf; sp != shapes_end; ++sp) {
@@ -1140,11 +1156,11 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                 e = (hipError_t)run_filter(sh, X, n0, false);
         }
         mark(2);
-        if (e == hipSuccess) e = (hipError_t)launch_upadd(A, ntm, lds_u, s);
+        if (e == hipSuccess && ntm > 0) e = (hipError_t)launch_upadd(A, ntm, lds_u, s);
         mark(3);
         if (prof)
             for (int i = 0; i < 3; ++i)
-                if (ev[i] && ev[i + 1]) g_prof_recs.push_back(ProfRec{i, ev[i], ev[i + 1]});
+                if (ev[i] && ev[i + 1] && (i != 0 || need_stage) && (i != 2 || ntm > 0)) g_prof_recs.push_back(ProfRec{i, ev[i], ev[i + 1]});
     }
     return e;
 }
@@ -1269,7 +1285,7 @@ static bool alloc_bank(spiir_bank* b)
     if (p.workspace == SPIIR_WORKSPACE_OWN) ok &= dalloc(&b->zw, p.zw_elems) == hipSuccess;
     ok &= dalloc(&b->uphist, (size_t)p.T * p.H * p.hu_len) == hipSuccess;
     ok &= dalloc(&b->flags, p.T) == hipSuccess;
-    ok &= dalloc(&b->clock, 2) == hipSuccess;
+    ok &= dalloc(&b->clock, 3) == hipSuccess;
     if (p.P > 1) {
         ok &= dalloc(&b->al, p.n_slots) == hipSuccess;
         ok &= dalloc(&b->uend, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
@@ -1731,7 +1747,7 @@ int spiir_load_state(spiir_bank* b, const void* host_buf, void* stream)
     upl(b->rings, sizeof(float) * p.ring_total);
     upl(b->uphist, sizeof(c32) * (size_t)p.T * p.H * p.hu_len);
     upl(b->flags, sizeof(int32_t) * p.T);
-    const int64_t clk[2] = {hdr.done, hdr.done};
+    const int64_t clk[3] = {hdr.done, hdr.done, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(b->clock, clk, sizeof(clk), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {

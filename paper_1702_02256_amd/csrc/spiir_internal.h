@@ -70,7 +70,7 @@ struct PieceDesc {
     int32_t run0;  // its level-2 runs are [run0, run1) (workgroup-local)
     int32_t run1;
     int32_t tmpl;
-    int32_t pad;
+    int32_t whole;  // it is its segment's only piece
 };
 
 // Per (template, band): its pieces' outputs, consecutive with stride max_block >> h.
@@ -114,7 +114,8 @@ struct BankDev {
     int32_t* flags;                 // [T] sticky non-finite flags
     // [0]: absolute base-rate index of the first sample of the chunk being
     // filtered; [1]: samples staged so far.  The staging kernel advances them,
-    // so a recorded launch sequence can be replayed block after block.
+    // so a recorded launch sequence can be replayed block after block.  [2]: the
+    // count of workgroups that have read the clock (requests without staging).
     int64_t* clock;
     // Parallel-in-time split (P > 1): band h's samples are cut at absolute
     // multiples of lc[h] (a multiple of C) into at most P + 1 chunks per block.
@@ -145,6 +146,10 @@ struct ReqArg {
     int32_t c0;          // offset of this chunk in the caller's block
     float thr2;          // threshold^2 of the trigger count
     int32_t nchunk;      // time-chunk slots per workgroup (1, or P + 1)
+    int32_t direct;      // no staging launch: the filter kernel reads x (single-rate banks)
+    int32_t z_direct;    // it also writes z for templates that are one piece
+    int32_t nblocks;     // workgroups of the request in the filter launch
+    int32_t T;           // its templates in the upsample-and-add launch (0: none needed)
 };
 
 // Everything one launch sequence needs, passed by value as kernel arguments.

@@ -50,6 +50,44 @@ __device__ __forceinline__ const SPIIR_AS_CONST T* cmem(const T* p)
 }
 typedef const SPIIR_AS_CONST BankDev CBankDev;
 
+// Waits for the wave's global loads (vmcnt 0).  Before a loop that stores: a
+// load whose wait the compiler cannot place on every path costs a wait in the
+// loop, and there it would also wait for the stores, a microsecond each time.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+// Requests that need no staging launch (single-rate banks, not split in time):
+// the filter kernel reads the block's new samples from x itself, its first
+// workgroup appends them to the band-0 ring, and the workgroup that is the last
+// to have read the device clock advances it.  The ring slots of the new samples
+// are none of those the block's history is read from, so no workgroup reads
+// what another writes.  With z written by the filter kernel too (piece_out), a
+// call is one launch where it was three: 1024 templates of 512 filters, 2048
+// samples, 282 -> 262 us; 2 templates, 74 samples 27 -> 20.
+//
+// First sample of the block; one thread reads it, before the ticket, so that
+// every workgroup has it when the last ticket advances the clock.
+__device__ __forceinline__ int64_t block_start(const ReqArg& q, CBankDev* bd, float* lds)
+{
+    if (!q.direct) return cmem(bd->clock)[0];  // set by the staging kernel
+    int64_t* w = reinterpret_cast<int64_t*>(lds);
+    if (threadIdx.x == 0) {
+        volatile int64_t* clock = bd->clock;
+        const int64_t s0 = clock[1];
+        *w = s0;
+        wait_loads();  // s0 has arrived before this workgroup is counted
+        unsigned* ticket = reinterpret_cast<unsigned*>(bd->clock + 2);
+        if (atomicAdd(ticket, 1u) == (unsigned)q.nblocks - 1u) {
+            *ticket = 0u;
+            clock[0] = s0;
+            clock[1] = s0 + q.n;
+        }
+    }
+    __syncthreads();
+    const int64_t s0 = *w;
+    __syncthreads();  // the words are reused
+    return s0;
+}
+
 // ---------------------------------------------------------------------------
 // Input staging and the downsample cascade (one workgroup per request).
 constexpr int kStageThreads = 1024;
@@ -61,6 +99,7 @@ __global__ void __launch_bounds__(kStageThreads) k_stage(LaunchArgs args)
     extern __shared__ float sm[];
     __shared__ long long s_base;
     const ReqArg& q = args.req[blockIdx.x];
+    if (q.direct) return;
     CBankDev* bd = cmem(q.bd);
     SPIIR_AS_GLOBAL int64_t* clock = gmem(bd->clock);
     const SPIIR_AS_GLOBAL float* x = gmem(q.x);
@@ -135,6 +174,53 @@ __global__ void __launch_bounds__(kStageThreads) k_stage(LaunchArgs args)
 // LDS: E0 [xcap] | E1 [xcap] (two copies only) | pbuf [L/2][kTile+1] c32 | l2 2 x [kTile][nrun_max] c32 |
 //      pzoff [npiece_max] i64 | lmeta [L] i32 | prun [npiece_max] int2
 // ---------------------------------------------------------------------------
+// Address of a piece's output row: the workspace, or for a single-rate template that
+// is one piece its row of z (no upsample-and-add pass over it then).
+__device__ __forceinline__ long long piece_out(const ReqArg& q, const PieceDesc& pd)
+{
+    c32* row = q.z_direct && pd.whole ? q.z + (int64_t)pd.tmpl * q.ldz : q.zw + pd.zoff;
+    return reinterpret_cast<long long>(row);
+}
+__device__ __forceinline__ SPIIR_AS_GLOBAL c32* piece_row(long long address)
+{
+    return gmem(reinterpret_cast<c32*>(address));
+}
+
+constexpr int kStageBatch = 4;  // window loads a thread keeps in flight
+
+// Fills the input window: E0[i] = fetch(i) for i < wn and, with two copies,
+// E1[i] = fetch(i + 1); kStageBatch loads in flight per thread before their
+// LDS stores.  (fetch(wn) is called, its value not used by any filter.)
+template <class Fetch>
+__device__ __forceinline__ void stage_window(float* E0, float* E1, int wn, Fetch fetch)
+{
+    const int nt = blockDim.x;
+    for (int i0 = threadIdx.x; i0 <= wn; i0 += kStageBatch * nt) {
+        float v[kStageBatch];
+#pragma unroll
+        for (int u = 0; u < kStageBatch; ++u) {
+            const int i = i0 + u * nt;
+            v[u] = i <= wn ? fetch(i) : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < kStageBatch; ++u) {
+            const int i = i0 + u * nt;
+            if (i < wn) E0[i] = v[u];
+            if (E1 && i > 0 && i <= wn) E1[i - 1] = v[u];
+        }
+    }
+}
+
+// The ring append of such a request (see block_start), by its first workgroup.
+__device__ __forceinline__ void append_block(const ReqArg& q, CBankDev* bd, int64_t s0)
+{
+    SPIIR_AS_GLOBAL float* ring = gmem(bd->rings + bd->ring_off[0]);
+    const int64_t mk = bd->ring_mask[0];
+    const SPIIR_AS_CONST float* x = cmem(q.x);
+#pragma unroll 4
+    for (int i = threadIdx.x; i < q.n; i += blockDim.x) ring[(s0 + i) & mk] = x[i];
+}
+
 // value of the other lane of the pair (lane ^ 1), via DPP quad_perm [1,0,3,2]
 __device__ __forceinline__ float pair_swap(float v)
 {
@@ -291,8 +377,6 @@ __device__ __forceinline__ Chunk chunk_range(int c, int nchunk, int64_t s0h, int
     return r;
 }
 
-constexpr int kStageBatch = 4;  // window loads a thread keeps in flight
-
 // LOCAL: the end-state pass of a time split (every chunk but the last runs
 // from zero, or the first from the carried state, and stores its end state;
 // no output).  Otherwise: the filter pass proper, each chunk starting from its
@@ -321,7 +405,9 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
     const int L = blockDim.x;
     const int tid = threadIdx.x;
     const int nh = q.n >> h;
-    const int64_t s0h = cmem(bd->clock)[0] >> h;  // set by the staging kernel of this chunk
+    const int64_t s0 = LOCAL ? cmem(bd->clock)[0] : block_start(q, bd, sm);
+    if (!LOCAL && q.direct && li == 0) append_block(q, bd, s0);
+    const int64_t s0h = s0 >> h;
     const Chunk ch = chunk_range(tc, q.nchunk, s0h, nh, bd->lc[h]);
     if (ch.k0 >= ch.k1 || (LOCAL && ch.last)) return;  // whole workgroup
     const int64_t cmask = bd->C - 1;
@@ -341,7 +427,7 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
     lmeta[tid] = cmem(bd->lane_meta)[wg.meta_base + tid];
     for (int p = tid; p < wg.npiece; p += L) {
         const PieceDesc pd = cmem(bd->piece)[wg.piece_base + p];
-        pzoff[p] = pd.zoff;
+        pzoff[p] = piece_out(q, pd);
         prun[p] = make_int2(pd.run0, pd.run1);
     }
 
@@ -412,8 +498,8 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 
     const int S = bd->S[h];
     const SPIIR_AS_CONST float* ring = cmem(bd->rings) + bd->ring_off[h];
+    const SPIIR_AS_CONST float* xblk = cmem(q.x);
     const int64_t mk = bd->ring_mask[h];
-    SPIIR_AS_GLOBAL c32* zwg = gmem(q.zw);
     // Lanes come in pairs of one run (segments span an even number of lanes).
     // The pair sum of sample j is entry e = lane/2 of row j: pbuf[e*(kTile+1) + j],
     // the even lane storing its real part and the odd lane its imaginary part.
@@ -428,21 +514,14 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
         const int64_t origin = ((s0h + kb - wg.maxd - 1) >> 6) << 6;
         const int wn = (int)(s0h + kb + sub - origin);
         __syncthreads();
-        // kStageBatch loads in flight per thread before their LDS stores
-        for (int i0 = tid; i0 <= wn; i0 += kStageBatch * L) {
-            float v[kStageBatch];
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int i = i0 + u * L;
-                v[u] = i <= wn ? ring[(origin + i) & mk] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int i = i0 + u * L;
-                if (i < wn) E0[i] = v[u];
-                if (two_copies && i > 0 && i <= wn) E1[i - 1] = v[u];
-            }
-        }
+        if (q.direct)
+            stage_window(E0, two_copies ? E1 : nullptr, wn, [&](int i) {
+                const int64_t a = origin + i;  // (a past the block's end is not used)
+                const SPIIR_AS_CONST float* p = a < s0 ? ring + (a & mk) : xblk + min((int)(a - s0), q.n - 1);
+                return *p;
+            });
+        else
+            stage_window(E0, two_copies ? E1 : nullptr, wn, [&](int i) { return ring[(origin + i) & mk]; });
         __syncthreads();
 
         int k = kb;
@@ -556,7 +635,7 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
                             accr += v.x;
                             acci += v.y;
                         }
-                        zwg[pzoff[p] + k + j] = c32{(float)accr, (float)acci};
+                        piece_row(pzoff[p])[k + j] = c32{(float)accr, (float)acci};
                     }
                 }
             }
@@ -655,12 +734,7 @@ __device__ __forceinline__ void split_step(const float (&xv)[NF], float& out, co
     if (SUM) out = split_sum<X, NF>(tr, ti);
 }
 
-// Waits for the wave's global loads (vmcnt 0).  A load whose wait the compiler
-// cannot place on every path costs a wait in the loop that follows, and there
-// it would also wait for the workspace stores, a microsecond each tile.
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
-
-// The same for LDS reads (lgkmcnt 0).
+// Waits for the wave's LDS reads (lgkmcnt 0).
 __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F); }
 
 // Keeps the LDS read before it from being fused with the next one (see
@@ -697,7 +771,9 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     const int ln = tid / X, part = tid % X;  // lane of the layout, thread of the lane
     const bool flip = part & 1;
     const int nh = q.n >> h;
-    const int64_t s0h = cmem(bd->clock)[0] >> h;
+    const int64_t s0 = LOCAL ? cmem(bd->clock)[0] : block_start(q, bd, sm);
+    if (!LOCAL && q.direct && li == 0) append_block(q, bd, s0);
+    const int64_t s0h = s0 >> h;
     const Chunk ch = chunk_range(tc, q.nchunk, s0h, nh, bd->lc[h]);
     if (ch.k0 >= ch.k1 || (LOCAL && ch.last)) return;  // whole workgroup
     const int64_t cmask = bd->C - 1;
@@ -716,7 +792,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     for (int i = tid; i < L; i += NT) lmeta[i] = cmem(bd->lane_meta)[wg.meta_base + i];
     for (int p = tid; p < wg.npiece; p += NT) {
         const PieceDesc pd = cmem(bd->piece)[wg.piece_base + p];
-        pzoff[p] = pd.zoff;
+        pzoff[p] = piece_out(q, pd);
         prun[p] = make_int2(pd.run0, pd.run1);
     }
     for (int i = tid; i < 2 * kTile * nrun; i += NT) l2buf[i] = c32{0.0f, 0.0f};
@@ -805,11 +881,12 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     const int p2 = min(t2 / (kComp * kTile), wg.npiece - 1);
     const int run0 = prun[p2].x, run1 = prun[p2].y;
     const bool long_run = __any(run1 - run0 > kRunAhead);
-    SPIIR_AS_GLOBAL float* zrow = reinterpret_cast<SPIIR_AS_GLOBAL float*>(gmem(q.zw) + pzoff[p2] + j2) + c2;
+    SPIIR_AS_GLOBAL float* zrow = reinterpret_cast<SPIIR_AS_GLOBAL float*>(piece_row(pzoff[p2]) + j2) + c2;
     const int l2off = 2 * (j2 * nrun + run0) + c2;
 
     const int S = bd->S[h];
     const SPIIR_AS_CONST float* ring = cmem(bd->rings) + bd->ring_off[h];
+    const SPIIR_AS_CONST float* xblk = cmem(q.x);
     const int64_t mk = bd->ring_mask[h];
     // Where the thread stores pair sums: of the X threads that hold the same
     // component of a pair, thread px stores every X-th sample.
@@ -925,7 +1002,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
                     sr += v[0];
                     if (X == 1) si += v[1];
                 }
-                SPIIR_AS_GLOBAL float* zp = reinterpret_cast<SPIIR_AS_GLOBAL float*>(gmem(q.zw) + pzoff[p] + k2 + j) + c;
+                SPIIR_AS_GLOBAL float* zp = reinterpret_cast<SPIIR_AS_GLOBAL float*>(piece_row(pzoff[p]) + k2 + j) + c;
                 zp[0] = (float)sr;
                 if (X == 1) zp[1] = (float)si;
             }
@@ -965,20 +1042,14 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         const int64_t origin = ((s0h + kb - wg.maxd - 1) >> 6) << 6;
         const int wn = (int)(s0h + kb + sub - origin);
         __syncthreads();
-        for (int i0 = tid; i0 <= wn; i0 += kStageBatch * NT) {
-            float v[kStageBatch];
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int i = i0 + u * NT;
-                v[u] = i <= wn ? ring[(origin + i) & mk] : 0.0f;
-            }
-#pragma unroll
-            for (int u = 0; u < kStageBatch; ++u) {
-                const int i = i0 + u * NT;
-                if (i < wn) E0[i] = v[u];
-                if (two_copies && i > 0 && i <= wn) E1[i - 1] = v[u];
-            }
-        }
+        if (q.direct)
+            stage_window(E0, two_copies ? E1 : nullptr, wn, [&](int i) {
+                const int64_t a = origin + i;  // (a past the block's end is not used)
+                const SPIIR_AS_CONST float* p = a < s0 ? ring + (a & mk) : xblk + min((int)(a - s0), q.n - 1);
+                return *p;
+            });
+        else
+            stage_window(E0, two_copies ? E1 : nullptr, wn, [&](int i) { return ring[(origin + i) & mk]; });
         wait_loads();
         __syncthreads();
 
@@ -1530,6 +1601,7 @@ __global__ void __launch_bounds__(kUpThreads, 4) k_upadd(LaunchArgs args)
 
     if (H == 1) {
         const SegDesc sg = seg[0];
+        if (q.z_direct && sg.npiece == 1) return;  // written by the filter kernel
         for (int k = tid; k < n; k += kUpThreads) {
             const c32 v = piece_sum(zw, sg, bd->zstride[0], k);
             if (zrow) zrow[k] = v;
