@@ -99,7 +99,7 @@ enum {
  *                         lane; fewer when a long delay window would not
  *                         fit the LDS).
  *   device                HIP device ordinal the bank lives on.
- *   time_chunks           P in {0, 1, 2, 4, ..., 64}; 0 or 1 = off;
+ *   time_chunks           P in {0, 1, 2, 4, ..., 64}; 0 or 1: none asked for;
  *                         SPIIR_TIME_CHUNKS_AUTO: the library picks P for
  *                         blocks of max_block samples, splitting while the
  *                         longest workgroup's run of dependent samples, cut
@@ -111,13 +111,18 @@ enum {
  *                         too small to fill the device finish sooner: every
  *                         band's samples are cut at absolute multiples of a
  *                         chunk length (a multiple of C, about the block /
- *                         P); an end-state pass runs all chunks but the last
+ *                         P, at least 64); an end-state pass runs all chunks
  *                         at once from zero state, a chain pass turns those
  *                         end states into each chunk's start state with
  *                         a1^length (computed in FP64 at create), and the
  *                         filter pass runs every chunk from its start state.
- *                         Results differ from P = 1 by rounding only (the
- *                         bitwise block-split invariance holds for P <= 1).
+ *                         Results differ from an unsplit bank's by rounding
+ *                         only; where blocks begin changes no bit of them,
+ *                         split or not.  The library splits very small banks
+ *                         by itself when neither this, filters_per_lane nor
+ *                         waves_per_group is given (spiir_plan then still
+ *                         reports 1; the footprint and the state include the
+ *                         split's arrays).
  *   window_copies         1 or 2; 0 = chosen by the library.  The filter
  *                         kernel keeps each band's input window in LDS, as
  *                         two copies shifted by one sample (each filter reads
@@ -369,7 +374,9 @@ int spiir_save_state(spiir_bank* bank, void* host_buf, void* hip_stream);
  * same shape and filter layout: the same sizes, launch shape and delays, as a
  * bank created from the same descriptor has.  The blob's header carries a
  * fingerprint of the layout; SPIIR_EINVAL (state unchanged) if the header does
- * not match.  Synchronous. */
+ * not match.  A blob of a bank split in time elsewhere, or not at all, is taken
+ * too (the outputs that follow differ by rounding only); its length follows from
+ * its header.  Synchronous. */
 int spiir_load_state(spiir_bank* bank, const void* host_buf, void* hip_stream);
 
 /* spiir_status — sticky non-finite flags.  Waits for the bank's work.

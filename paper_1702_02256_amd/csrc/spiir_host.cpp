@@ -33,8 +33,10 @@ constexpr int kNoFit = 1;           // internal: this launch shape exceeds the L
 constexpr int kXcapMax = 24576;     // LDS window, floats
 constexpr int kMaxLds = 160 * 1024;
 constexpr int kComputeUnits = 256;  // MI355X
+constexpr int kDualSamples = 256;   // shortest block of a bank split in time that runs in chunks
 constexpr uint32_t kStateMagic = 0x53504952u;  // "SPIR"
 constexpr uint32_t kStateVersion = 3;  // 3: 128-byte header with the layout fingerprint
+constexpr uint32_t kStateVersionSplit = 4;  // 4: and at the end the carried state of a time split
 constexpr int64_t kStateHeaderBytes = 128;
 
 int default_filters_per_lane(const spiir_bank_desc* d)
@@ -54,7 +56,8 @@ int64_t next_pow2(int64_t v)
 struct Plan {
     int T = 0, H = 0, L = 0, F = 0, W = 0, C = 0, precision = 0;
     int td = 0, tu = 0, hu_len = 0, max_block = 0, mb_inner = 0;
-    int P = 1;
+    int P = 1;            // time chunks per block
+    int time_chunks = 1;  // of them, those the caller asked for
     int lc[SPIIR_MAX_BANDS] = {};
     int xcap = 0, copies = 2;
     int nrun_max = 1, npiece_max = 1;
@@ -78,6 +81,36 @@ struct Plan {
     size_t footprint = 0;
     uint64_t layout = 0;  // layout_fingerprint, taken before the arrays are released
 };
+
+// Device bytes of a time split: a1^lc in two parts, end and start states of
+// the chunks, and six arrays of carried and entering state.
+size_t split_bytes(const Plan& p)
+{
+    return p.P > 1 ? (size_t)p.n_slots * sizeof(c32) * (2 + 2 * (size_t)(p.P + 1) + 6) : 0;
+}
+
+// Chunk length per band of a split in P: a multiple of C, at least four tiles
+// (shorter chunks cost more in their workgroups' starts than they save),
+// covering the band's share of the largest launch in P pieces, so a block
+// meets at most P + 1 chunks.
+void set_chunks(Plan& p, int P)
+{
+    p.P = P;
+    for (int h = 0; h < p.H; ++h) {
+        const int mbh = std::max(p.mb_inner >> h, 1);
+        const int per = (mbh + P - 1) / P;
+        p.lc[h] = (std::max(per, 4 * kTile) + p.C - 1) / p.C * p.C;
+    }
+}
+
+// Chunks of band h that a request can meet (workgroups per filter workgroup of the
+// plan in its launch).
+int chunk_slots(const Plan& p, int h, const ReqArg& q)
+{
+    if (q.nchunk == 1) return 1;
+    const int64_t nh = q.n >> h;
+    return (int)((nh + p.lc[h] - 1) / p.lc[h]) + 1;
+}
 
 bool finite_all(const double* p, int64_t n)
 {
@@ -151,14 +184,8 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
     p.td = p.H > 1 ? d->n_taps_down : 1;
     p.tu = p.H > 1 ? d->n_taps_up : 1;
     p.hu_len = (p.tu + 1) / 2;
-    p.P = d->time_chunks > 1 ? d->time_chunks : 1;
-    // chunk length per band: a multiple of C covering the band's share of the
-    // largest launch in P pieces, so a block meets at most P + 1 chunks
-    for (int h = 0; h < p.H; ++h) {
-        const int mbh = std::max(p.mb_inner >> h, 1);
-        const int per = (mbh + p.P - 1) / p.P;
-        p.lc[h] = std::max(p.C, (per + p.C - 1) / p.C * p.C);
-    }
+    p.time_chunks = d->time_chunks > 1 ? d->time_chunks : 1;
+    set_chunks(p, p.time_chunks);
     const int T = p.T, H = p.H, L = p.L, F = p.F;
 
     std::vector<int64_t> moff((size_t)T * H);
@@ -457,8 +484,7 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
     if (p.workspace == SPIIR_WORKSPACE_OWN) fp += (size_t)p.zw_elems * sizeof(c32);
     fp += (size_t)T * H * p.hu_len * sizeof(c32) + (size_t)T * sizeof(int32_t) + sizeof(BankDev);
     fp += 3 * sizeof(int64_t);
-    if (p.P > 1)  // a1^lc, end states, chained states, entering chunk-start state, exponents
-        fp += (size_t)p.n_slots * sizeof(c32) * (1 + 2 * (size_t)(p.P + 1) + 1);
+    fp += split_bytes(p);
     p.footprint = fp;
     p.n_groups = (int32_t)p.wg.size();
     p.n_pieces = (int32_t)p.piece.size();
@@ -614,6 +640,29 @@ int auto_time_chunks(const Plan& p)
     return P;
 }
 
+// Time chunks of a bank that asks for none and leaves the launch shape to the
+// library.  The split adds an end-state pass, about half as much work again, so
+// it is kept to banks of which even the largest batch cannot be slowed down by
+// it much: SPIIR_MAX_BATCH of them make at most one workgroup of 256 lanes per
+// compute unit, as long as their longest.  Measured at that limit (45 templates, 5
+// bands, max_block 4096), us per call not split / split: blocks of 4096, 1024,
+// 256, 64 samples alone 349 / 90, 101 / 66, 55 / 55, 30 / 32, in a batch of 16 banks
+// 619 / 551, 225 / 232, 128 / 144, 105 / 124; one template of 128 filters, 4096
+// samples 151 / 37.
+int small_bank_chunks(const Plan& p)
+{
+    int64_t work = 0, longest = 0;
+    for (const WgDesc& w : p.wg) {
+        const int64_t nh = std::max(p.mb_inner >> w.band, 1);
+        work += nh;
+        longest = std::max(longest, nh);
+    }
+    if (work == 0 || work * p.L * SPIIR_MAX_BATCH > longest * 256 * kComputeUnits) return 1;
+    int P = 1;
+    while (P < 16 && longest >= 2 * P * 64) P *= 2;  // chunks of 64 samples or more
+    return P;
+}
+
 // The matrix-core engine's layout (single-rate banks): every template's
 // filters fill workgroups of kMfmaSlots slots, one template per workgroup
 // (a template with more filters gets several, each a piece of its output),
@@ -761,7 +810,17 @@ int make_plan_mfma(const spiir_bank_desc* d, Plan& p)
 int make_plan(const spiir_bank_desc* d, Plan& p)
 {
     if (d && d->engine == SPIIR_ENGINE_MFMA) return make_plan_mfma(d, p);
-    if (!d || d->time_chunks != SPIIR_TIME_CHUNKS_AUTO) return make_plan_fixed(d, p);
+    if (!d || d->time_chunks != SPIIR_TIME_CHUNKS_AUTO) {
+        const int rc = make_plan_fixed(d, p);
+        if (rc == SPIIR_OK && p.P == 1 && !d->filters_per_lane && !d->waves_per_group) {
+            const int P = small_bank_chunks(p);
+            if (P > 1) {
+                set_chunks(p, P);
+                p.footprint += split_bytes(p);
+            }
+        }
+        return rc;
+    }
     spiir_bank_desc d1 = *d;
     d1.time_chunks = 0;
     int rc = make_plan_fixed(&d1, p);
@@ -837,7 +896,8 @@ struct spiir_bank {
     c32* uphist = nullptr;
     int32_t* flags = nullptr;
     int64_t* clock = nullptr;
-    c32 *al = nullptr, *uend = nullptr, *schain = nullptr, *ys0 = nullptr;
+    c32 *al = nullptr, *uend = nullptr, *schain = nullptr;  // time split
+    c32 *s = nullptr, *ey = nullptr, *eu = nullptr, *y0 = nullptr, *ys0 = nullptr, *euend = nullptr;
     c32 *kc = nullptr, *pw = nullptr;  // matrix-core engine tables
     BankDev* bd = nullptr;
 };
@@ -856,7 +916,8 @@ void free_bank(spiir_bank* b)
 {
     if (!b) return;
     void* ptrs[] = {b->a,     b->b,     b->dc, b->y,  b->ys, b->off, b->wg,     b->piece, b->seg,
-                    b->lane_meta, b->rings, b->hd, b->hu, b->zw, b->uphist, b->flags, b->clock, b->al, b->uend, b->schain, b->ys0,
+                    b->lane_meta, b->rings, b->hd, b->hu, b->zw, b->uphist, b->flags, b->clock, b->al, b->uend, b->schain,
+                    b->s, b->ey, b->eu, b->y0, b->ys0, b->euend,
                     b->kc, b->pw, b->bd};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -870,6 +931,12 @@ int zero_state(spiir_bank* b, hipStream_t s)
     int e = 0;
     e |= launch_fill(b->y, p.n_slots * (int64_t)sizeof(c32), s);
     e |= launch_fill(b->ys, p.n_slots * (int64_t)sizeof(c32), s);
+    if (p.P > 1) {
+        // uend and euend too: lanes of padding that a launch leaves out never
+        // write theirs, and k_chain reads every slot's
+        for (c32* a : {b->s, b->ey, b->eu, b->euend}) e |= launch_fill(a, p.n_slots * (int64_t)sizeof(c32), s);
+        e |= launch_fill(b->uend, (p.P + 1) * p.n_slots * (int64_t)sizeof(c32), s);
+    }
     e |= launch_fill(b->rings, p.ring_total * (int64_t)sizeof(float), s);
     e |= launch_fill(b->uphist, (int64_t)p.T * p.H * p.hu_len * (int64_t)sizeof(c32), s);
     e |= launch_fill(b->flags, (int64_t)p.T * (int64_t)sizeof(int32_t), s);
@@ -886,7 +953,8 @@ size_t workspace_bytes(const Plan& p)
 int64_t state_bytes(const Plan& p)
 {
     return kStateHeaderBytes + p.n_slots * 2 * (int64_t)sizeof(c32) + p.ring_total * (int64_t)sizeof(float) +
-           (int64_t)p.T * p.H * p.hu_len * (int64_t)sizeof(c32) + (int64_t)p.T * 4;
+           (int64_t)p.T * p.H * p.hu_len * (int64_t)sizeof(c32) + (int64_t)p.T * 4 +
+           (p.P > 1 ? 3 * p.n_slots * (int64_t)sizeof(c32) : 0);
 }
 
 struct StateHeader {
@@ -895,6 +963,7 @@ struct StateHeader {
     int64_t n_slots, ring_total, done;
     int64_t hist;
     uint64_t layout;  // layout_fingerprint of the bank that wrote the blob
+    int32_t lc0;      // version 4: chunk length of band 0
 };
 static_assert(sizeof(StateHeader) <= kStateHeaderBytes, "state header");
 
@@ -976,15 +1045,16 @@ const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 // 78 / 61 / 71 and 86 / 108 / 84.  X = 4 pays where a workgroup is at most 128
 // lanes, so that the four threads still make two waves per SIMD: one
 // template of 128 filters, 4096 samples 586 (k_filter), 143 (X = 4), 203 (X = 2).
-// Runs of fewer than 64 samples (time chunks of 32) lose to the two tiles the
-// pipeline needs to fill, 39 / 44; 512 lanes leave no room for more threads, and
+// Short runs lose to the two tiles the pipeline needs to fill: chunks of 32
+// samples 39 / 44, 64 samples of 4 banks of 60 multi-rate templates 47 / 50 (X = 2),
+// of 16 such banks 110 / 134 (X = 1; 256 samples 139 / 144); 512 lanes leave no room for more threads, and
 // X = 1 there gains nothing (530 / 562; 1024 single-rate templates 301 / 303).
 int pipe_threads(int F, int lanes, int longest, double rounds)
 {
     const double g = rounds * lanes / (256.0 * kComputeUnits);
-    if (F != 4 || 2 * lanes > kPipeThreads || longest < 4 * kTile || g > 2.0) return 0;
-    if (g > 1.0) return 1;
-    return 4 * lanes <= kPipeThreads ? 4 : 2;
+    if (F != 4 || 2 * lanes > kPipeThreads || g > 2.0) return 0;
+    const int x = g > 1.0 ? 1 : 4 * lanes <= kPipeThreads ? 4 : 2;
+    return longest >= (x == 1 ? 32 : x == 2 ? 8 : 4) * kTile ? x : 0;
 }
 
 // Kernels of one batch on `s`: per inner chunk of at most kInnerBlock base-rate
@@ -1021,16 +1091,9 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             ra.H = p.H;
             ra.c0 = (int32_t)c0;
             ra.thr2 = thr2;
-            ra.nchunk = p.P > 1 ? p.P + 1 : 1;
-            // a single-rate bank needs neither the cascade nor, where every
-            // template is one piece and z is wanted, the upsample-and-add pass
-            // (time chunks of a few tiles gain nothing from it: each of their
-            // workgroups would wait for the clock)
-            ra.direct = p.H == 1 && p.engine == SPIIR_ENGINE_VALU && p.n_groups > 0 && p.P == 1;
-            ra.nblocks = p.n_groups;
-            ra.z_direct = ra.direct && ra.z && !ra.peaks;
-            ra.T = ra.z_direct && p.whole_templates ? 0 : p.T;
-            need_stage |= !ra.direct;
+            // (dual: see below)
+            ra.dual = p.P > 1 && p.F == 4 && ra.n <= std::max(2 * p.lc[0], kDualSamples);
+            ra.nchunk = p.P > 1 && !ra.dual ? p.P + 1 : 1;
             lds_s = std::max(lds_s, p.lds_stage);
             lds_u = std::max(lds_u, p.lds_up);
             maxH = std::max(maxH, p.H);
@@ -1055,6 +1118,50 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             if (!seen) shape_buf[nshape++] = shape_of(k);
         }
         const Shape* const shapes_end = shape_buf + nshape;
+        // how full a shape's launch over the requests of X makes the device (pipe_threads)
+        auto threads_of = [&](const Shape& sh, const LaunchArgs& X, int* lanes_out) {
+            int64_t work = 0;  // samples of all workgroups, and of the longest
+            int longest = 1, lanes = 64;
+            bool dual = false;
+            for (int k = 0; k < X.nreq; ++k) {
+                const Plan& p = req[rmap[k]].bank->plan;
+                if (!same(shape_of(k), sh)) continue;
+                lanes = std::max(lanes, p.lanes_used);
+                dual |= X.req[k].dual != 0;
+                for (int h = 0; h < p.H; ++h) {
+                    const int nwg = p.band_wg0[h + 1] - p.band_wg0[h], nh = X.req[k].n >> h;
+                    if (nwg == 0) continue;
+                    work += (int64_t)nwg * nh;
+                    longest = std::max(longest, X.req[k].nchunk > 1 ? std::min(nh, p.lc[h]) : nh);
+                }
+            }
+            if (lanes_out) *lanes_out = lanes;
+            return pipe_threads(sh.F, lanes, dual ? std::max(longest, 8 * kTile) : longest, (double)work / longest);
+        };
+        // A short block of a bank split in time (two chunks) runs in one launch,
+        // its chunks in turn in one workgroup that carries both runs, where
+        // the pipelined kernel has the registers (X > 1).  One template, 7
+        // bands: 64 samples 42 (in chunks) / 28 us, 256 samples 44 / 35.
+        for (const Shape* sp = shape_buf; sp != shapes_end; ++sp)
+            if (threads_of(*sp, A, nullptr) < 2)
+                for (int k = 0; k < A.nreq; ++k)
+                    if (same(shape_of(k), *sp) && A.req[k].dual) {
+                        A.req[k].dual = 0;
+                        A.req[k].nchunk = req[rmap[k]].bank->plan.P + 1;
+                    }
+        for (int k = 0; k < A.nreq; ++k) {
+            const Plan& p = req[rmap[k]].bank->plan;
+            ReqArg& ra = A.req[k];
+            // a single-rate bank needs neither the cascade nor, where every
+            // template is one piece and z is wanted, the upsample-and-add pass
+            ra.direct = p.H > 1 || p.engine != SPIIR_ENGINE_VALU || p.n_groups == 0 ? 0
+                        : ra.nchunk > 1                                              ? kDirectSplit
+                                                                                    : kDirect;
+            ra.nblocks = p.n_groups;
+            ra.z_direct = ra.direct && ra.z && !ra.peaks;
+            ra.T = ra.z_direct && p.whole_templates ? 0 : p.T;
+            need_stage |= !ra.direct;
+        }
         // filter workgroups of one shape: band-major across requests (longest
         // bands first), chunk-major inside a (band, request) segment when split
         // in time
@@ -1067,7 +1174,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                     const Plan& p = req[rmap[k]].bank->plan;  // X keeps A's request order
                     if (h >= p.H || !same(shape_of(k), sh)) continue;
                     if (split_only && X.req[k].nchunk == 1) continue;
-                    const int cnt = (p.band_wg0[h + 1] - p.band_wg0[h]) * X.req[k].nchunk;
+                    const int cnt = (p.band_wg0[h + 1] - p.band_wg0[h]) * chunk_slots(p, h, X.req[k]);
                     if (cnt == 0) continue;
                     X.seg_req[X.nseg] = (int16_t)k;
                     X.seg_band[X.nseg] = (int16_t)h;
@@ -1118,21 +1225,14 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         auto run_filter = [&](const Shape& sh, const LaunchArgs& X, int nblocks, bool local) {
             const int lds = shape_lds(sh, local);
             if (sh.engine == SPIIR_ENGINE_MFMA) return launch_filter_mfma(X, nblocks, lds, s);
-            int64_t work = 0;  // samples of all workgroups, and of the longest
-            int longest = 1, lanes = 64;
-            for (int k = 0; k < X.nreq; ++k) {
-                const Plan& p = req[rmap[k]].bank->plan;
-                if (!same(shape_of(k), sh)) continue;
-                lanes = std::max(lanes, p.lanes_used);
-                for (int h = 0; h < p.H; ++h) {
-                    const int nwg = p.band_wg0[h + 1] - p.band_wg0[h], nh = X.req[k].n >> h;
-                    if (nwg == 0) continue;
-                    work += (int64_t)nwg * nh;
-                    longest = std::max(longest, X.req[k].nchunk > 1 ? std::min(nh, p.lc[h]) : nh);
-                }
+            int lanes = 0;
+            const int x = threads_of(sh, X, &lanes);
+            if (x) {
+                bool dual = false;
+                for (int k = 0; k < X.nreq; ++k) dual |= X.req[k].dual && same(shape_of(k), sh);
+                const PipeMode mode = local ? PipeMode::kLocal : dual ? PipeMode::kDual : PipeMode::kFilter;
+                return launch_filter_pipe(x, mode, sh.prec, X, nblocks, lanes, lds, s);
             }
-            const int x = pipe_threads(sh.F, lanes, longest, (double)work / longest);
-            if (x) return launch_filter_pipe(x, local, sh.prec, X, nblocks, lanes, lds, s);
             return local ? launch_filter_local(sh.F, sh.prec, X, nblocks, sh.L, lds, s)
                          : launch_filter(sh.F, sh.prec, X, nblocks, sh.L, lds, s);
         };
@@ -1222,7 +1322,7 @@ static void fill_plan_info(const Plan& p, spiir_plan_info* info)
     info->lds_bytes = p.lds_filter;
     info->carry_chunk = p.C;
     info->footprint = p.footprint;
-    info->time_chunks = p.P;
+    info->time_chunks = p.time_chunks;
     info->window_copies = p.copies;
     info->workspace_bytes = workspace_bytes(p);
     info->workspace = p.workspace;
@@ -1287,10 +1387,11 @@ static bool alloc_bank(spiir_bank* b)
     ok &= dalloc(&b->flags, p.T) == hipSuccess;
     ok &= dalloc(&b->clock, 3) == hipSuccess;
     if (p.P > 1) {
-        ok &= dalloc(&b->al, p.n_slots) == hipSuccess;
+        ok &= dalloc(&b->al, 2 * (size_t)p.n_slots) == hipSuccess;
         ok &= dalloc(&b->uend, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
         ok &= dalloc(&b->schain, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
-        ok &= dalloc(&b->ys0, p.n_slots) == hipSuccess;
+        for (c32** a : {&b->s, &b->ey, &b->eu, &b->y0, &b->ys0, &b->euend})
+            ok &= dalloc(a, p.n_slots) == hipSuccess;
     }
     if (p.engine == SPIIR_ENGINE_MFMA) {
         ok &= dalloc(&b->kc, (size_t)p.n_slots * kMfmaT) == hipSuccess;
@@ -1351,7 +1452,12 @@ static BankDev bank_dev(const spiir_bank* b)
     bd.al = b->al;
     bd.uend = b->uend;
     bd.schain = b->schain;
+    bd.s = b->s;
+    bd.ey = b->ey;
+    bd.eu = b->eu;
+    bd.y0 = b->y0;
     bd.ys0 = b->ys0;
+    bd.euend = b->euend;
     bd.engine = p.engine;
     bd.kc = b->kc;
     bd.pw = b->pw;
@@ -1570,7 +1676,7 @@ int spiir_clone(const spiir_bank* src, void* stream, spiir_bank** out)
     dd(b->lane_meta, src->lane_meta, sizeof(int32_t) * (size_t)p.n_groups * p.L);
     dd(b->hd, src->hd, sizeof(float) * p.td);
     dd(b->hu, src->hu, sizeof(float) * p.tu);
-    if (p.P > 1) dd(b->al, src->al, sizeof(c32) * p.n_slots);
+    if (p.P > 1) dd(b->al, src->al, 2 * sizeof(c32) * p.n_slots);
     if (p.engine == SPIIR_ENGINE_MFMA) {
         dd(b->kc, src->kc, sizeof(c32) * p.n_slots * kMfmaT);
         dd(b->pw, src->pw, sizeof(c32) * p.n_slots * kMfmaT);
@@ -1697,9 +1803,9 @@ int spiir_save_state(spiir_bank* b, void* host_buf, void* stream)
     if (hipSetDevice(b->device) != hipSuccess) return SPIIR_EDEVICE;
     hipError_t e = hipSuccess;
     if (b->ev_recorded) e = hipStreamWaitEvent(s, b->ev, 0);
-    StateHeader hdr{kStateMagic, kStateVersion, p.T, p.H, p.F, p.L, p.C, p.precision,
+    StateHeader hdr{kStateMagic, p.P > 1 ? kStateVersionSplit : kStateVersion, p.T, p.H, p.F, p.L, p.C, p.precision,
                     p.n_slots, p.ring_total, b->done, (int64_t)p.T * p.H * p.hu_len,
-                    p.layout};
+                    p.layout, p.P > 1 ? p.lc[0] : 0};
     char* o = (char*)host_buf;
     std::memset(o, 0, kStateHeaderBytes);
     std::memcpy(o, &hdr, sizeof(hdr));
@@ -1713,6 +1819,8 @@ int spiir_save_state(spiir_bank* b, void* host_buf, void* stream)
     dn(b->rings, sizeof(float) * p.ring_total);
     dn(b->uphist, sizeof(c32) * (size_t)p.T * p.H * p.hu_len);
     dn(b->flags, sizeof(int32_t) * p.T);
+    if (p.P > 1)
+        for (const c32* a : {b->s, b->ey, b->eu}) dn(a, sizeof(c32) * p.n_slots);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {
         b->poisoned = true;
@@ -1728,11 +1836,22 @@ int spiir_load_state(spiir_bank* b, const void* host_buf, void* stream)
     const Plan& p = b->plan;
     StateHeader hdr;
     std::memcpy(&hdr, host_buf, sizeof(hdr));
-    if (hdr.magic != kStateMagic || hdr.version != kStateVersion || hdr.T != p.T || hdr.H != p.H ||
+    if (hdr.magic != kStateMagic || (hdr.version != kStateVersion && hdr.version != kStateVersionSplit) ||
+        hdr.T != p.T || hdr.H != p.H ||
         hdr.F != p.F || hdr.L != p.L || hdr.C != p.C || hdr.n_slots != p.n_slots ||
         hdr.ring_total != p.ring_total || hdr.hist != (int64_t)p.T * p.H * p.hu_len || hdr.done < 0 ||
         hdr.done % (1 << (p.H - 1)) != 0 || hdr.layout != p.layout)
         return SPIIR_EINVAL;
+    const bool rebuild = p.P > 1 && !(hdr.version == kStateVersionSplit && hdr.lc0 == p.lc[0]);
+    std::vector<c32> rs, rey, reu;  // in use until the synchronisation below
+    try {
+        if (rebuild) {
+            rs.assign((size_t)p.n_slots, c32{0.0f, 0.0f});
+            rey = reu = rs;
+        }
+    } catch (const std::bad_alloc&) {
+        return SPIIR_ENOMEM;
+    }
     int rc = bank_sync(b);
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
@@ -1747,6 +1866,27 @@ int spiir_load_state(spiir_bank* b, const void* host_buf, void* stream)
     upl(b->rings, sizeof(float) * p.ring_total);
     upl(b->uphist, sizeof(c32) * (size_t)p.T * p.H * p.hu_len);
     upl(b->flags, sizeof(int32_t) * p.T);
+    if (p.P > 1 && !rebuild) {
+        for (c32* a : {b->s, b->ey, b->eu}) upl(a, sizeof(c32) * p.n_slots);
+    } else if (p.P > 1) {
+        // a state without them, or split at other places: the state at the
+        // restart is the start state where the restart is a chunk's start, else
+        // it stands for the zero-start run (from a start state of zero, the sum of
+        // the two is what the chunks that follow are formed from)
+        const c32* y = (const c32*)((const char*)host_buf + kStateHeaderBytes);
+        const int64_t per_wg = (int64_t)p.F * p.L;
+        for (int h = 0; h < p.H; ++h) {
+            const bool start = (hdr.done >> h) % p.lc[h] == 0;
+            for (int64_t g = p.band_wg0[h] * per_wg; g < p.band_wg0[h + 1] * per_wg; ++g) {
+                std::memcpy(start ? &rs[g] : &rey[g], y + g, sizeof(c32));
+                if (!start) std::memcpy(&reu[g], y + p.n_slots + g, sizeof(c32));
+            }
+        }
+        const std::vector<c32>* from[3] = {&rs, &rey, &reu};
+        c32* to[3] = {b->s, b->ey, b->eu};
+        for (int i = 0; i < 3 && e == hipSuccess; ++i)
+            e = hipMemcpyAsync(to[i], from[i]->data(), sizeof(c32) * p.n_slots, hipMemcpyHostToDevice, s);
+    }
     const int64_t clk[3] = {hdr.done, hdr.done, 0};
     if (e == hipSuccess) e = hipMemcpyAsync(b->clock, clk, sizeof(clk), hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);

@@ -122,10 +122,15 @@ struct BankDev {
     int32_t P;
     int32_t lc[kMaxBands];
     int64_t n_slots;
-    const c32* al;                  // per slot: a1^lc (FP64 -> FP32), same form as `a`
+    const c32* al;                  // per slot: fl32(a1^lc), then [n_slots] the rest, same form as `a`
     c32* uend;                      // [P+1][n_slots] chunk end states from zero start
-    c32* schain;                    // [P+1][n_slots] chained chunk start states
-    c32* ys0;                       // [n_slots] pending carry correction entering the block
+    c32* schain;                    // [P+1][n_slots] chunk start states
+    // [n_slots] each, carried: the start state of the chunk in progress, its
+    // zero-start state so far and that run's pending carry correction
+    c32 *s, *ey, *eu;
+    // [n_slots] each, within a block: y and ys entering it, the last chunk's
+    // pending carry correction
+    c32 *y0, *ys0, *euend;
     // Matrix-core engine (engine == SPIIR_ENGINE_MFMA): `a` holds fl32(a1^8),
     // `dc` the chunk-chain carry correction a1^C - fl32(a1^8)^(C/8), and
     //   kc[8*slot + j] = b0 a1^j, pw[8*slot + t] = a1^(t+1), j, t < 8.
@@ -133,6 +138,10 @@ struct BankDev {
     const c32* kc;
     const c32* pw;
 };
+
+// No staging launch (single-rate banks): the filter kernel reads x itself, or
+// for a bank split in time its end-state pass does.
+constexpr int kDirect = 1, kDirectSplit = 2;
 
 struct ReqArg {
     const BankDev* bd;
@@ -145,8 +154,9 @@ struct ReqArg {
     int32_t H;
     int32_t c0;          // offset of this chunk in the caller's block
     float thr2;          // threshold^2 of the trigger count
-    int32_t nchunk;      // time-chunk slots per workgroup (1, or P + 1)
-    int32_t direct;      // no staging launch: the filter kernel reads x (single-rate banks)
+    int32_t nchunk;      // 1, or most time chunks of a band (split in time)
+    int32_t dual;        // split in time, but a short block: one workgroup runs its chunks in turn
+    int32_t direct;      // who stages the block: 0, kDirect or kDirectSplit
     int32_t z_direct;    // it also writes z for templates that are one piece
     int32_t nblocks;     // workgroups of the request in the filter launch
     int32_t T;           // its templates in the upsample-and-add launch (0: none needed)
@@ -176,9 +186,11 @@ int launch_prep(const c64* a, const c64* b, int64_t n, int C, c32* fa, c32* fb, 
                 const int32_t* slot_lc, c32* fal, void* stream);
 int launch_filter_local(int F, int precision, const LaunchArgs& a, int nblocks, int L, int lds_bytes,
                         void* stream);
-// F = 4 only: the pipelined filter kernel with X threads per lane, X in {1, 2, 4}
-// (its end-state pass with `local`).
-int launch_filter_pipe(int X, bool local, int precision, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
+// F = 4 only: the pipelined filter kernel with X threads per lane, X in {1, 2, 4};
+// as the filter pass, the end-state pass of a time split, or (X > 1) the filter
+// pass that also runs the zero-start run of requests with `dual`.
+enum class PipeMode { kFilter, kLocal, kDual };
+int launch_filter_pipe(int X, PipeMode mode, int precision, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
                        void* stream);
 int launch_chain(const LaunchArgs& a, int64_t nblocks, void* stream);
 int launch_fill(void* p, int64_t bytes, void* stream);

@@ -55,12 +55,13 @@ typedef const SPIIR_AS_CONST BankDev CBankDev;
 // loop, and there it would also wait for the stores, a microsecond each time.
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Requests that need no staging launch (single-rate banks, not split in time):
+// Requests that need no staging launch (single-rate banks):
 // the filter kernel reads the block's new samples from x itself, its first
 // workgroup appends them to the band-0 ring, and the workgroup that is the last
 // to have read the device clock advances it.  The ring slots of the new samples
 // are none of those the block's history is read from, so no workgroup reads
-// what another writes.  With z written by the filter kernel too (piece_out), a
+// what another writes.  A bank split in time is staged the same way by its
+// end-state pass, and k_chain advances the clock.  With z written by the filter kernel too (piece_out), a
 // call is one launch where it was three: 1024 templates of 512 filters, 2048
 // samples, 282 -> 262 us; 2 templates, 74 samples 27 -> 20.
 //
@@ -68,7 +69,6 @@ __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70
 // every workgroup has it when the last ticket advances the clock.
 __device__ __forceinline__ int64_t block_start(const ReqArg& q, CBankDev* bd, float* lds)
 {
-    if (!q.direct) return cmem(bd->clock)[0];  // set by the staging kernel
     int64_t* w = reinterpret_cast<int64_t*>(lds);
     if (threadIdx.x == 0) {
         volatile int64_t* clock = bd->clock;
@@ -217,8 +217,15 @@ __device__ __forceinline__ void append_block(const ReqArg& q, CBankDev* bd, int6
     SPIIR_AS_GLOBAL float* ring = gmem(bd->rings + bd->ring_off[0]);
     const int64_t mk = bd->ring_mask[0];
     const SPIIR_AS_CONST float* x = cmem(q.x);
-#pragma unroll 4
-    for (int i = threadIdx.x; i < q.n; i += blockDim.x) ring[(s0 + i) & mk] = x[i];
+    for (int i0 = threadIdx.x; i0 < q.n; i0 += kStageBatch * blockDim.x) {
+        float v[kStageBatch];
+#pragma unroll
+        for (int u = 0; u < kStageBatch; ++u) v[u] = x[min(i0 + u * (int)blockDim.x, q.n - 1)];
+#pragma unroll
+        for (int u = 0; u < kStageBatch; ++u)
+            if (i0 + u * (int)blockDim.x < q.n) ring[(s0 + i0 + u * (int)blockDim.x) & mk] = v[u];
+    }
+    if (q.direct == kDirectSplit && threadIdx.x == 0) gmem(bd->clock)[0] = s0;  // k_chain advances [1]
 }
 
 // value of the other lane of the pair (lane ^ 1), via DPP quad_perm [1,0,3,2]
@@ -347,11 +354,13 @@ __device__ __forceinline__ void tile_partial(const float* const (&xp)[F], int cn
 }
 
 // Time chunk c of a band's block [s0h, s0h + nh) when the bank is split in
-// time: chunk 0 runs from the block start to the first absolute multiple of
-// lc, chunk c >= 1 covers [B + (c-1) lc, B + c lc) clipped to the block.
+// time, at absolute multiples of lc: chunk 0 is the rest of the chunk in
+// progress (from the block start to the first multiple; empty if the block
+// starts on one), chunk c >= 1 covers [B + (c-1) lc, B + c lc) clipped to the
+// block.
 struct Chunk {
-    int k0, k1;       // block-relative sample range (empty if k0 >= k1)
-    bool first, last; // first / last non-empty chunk of the block
+    int k0, k1;  // block-relative sample range (empty if k0 >= k1)
+    bool last;   // last non-empty chunk of the block
 };
 
 __device__ __forceinline__ Chunk chunk_range(int c, int nchunk, int64_t s0h, int nh, int lc)
@@ -360,11 +369,10 @@ __device__ __forceinline__ Chunk chunk_range(int c, int nchunk, int64_t s0h, int
     if (nchunk == 1) {
         r.k0 = 0;
         r.k1 = nh;
-        r.first = r.last = true;
+        r.last = true;
         return r;
     }
     const int64_t B = (s0h + lc - 1) / lc * lc;
-    const int first_c = B == s0h ? 1 : 0;
     const int last_c = s0h + nh - 1 < B ? 0 : 1 + (int)((s0h + nh - 1 - B) / lc);
     int64_t cs = c == 0 ? s0h : B + (int64_t)(c - 1) * lc;
     int64_t ce = c == 0 ? B : cs + lc;
@@ -372,15 +380,43 @@ __device__ __forceinline__ Chunk chunk_range(int c, int nchunk, int64_t s0h, int
     if (ce > s0h + nh) ce = s0h + nh;
     r.k0 = (int)(cs - s0h);
     r.k1 = ce > cs ? (int)(ce - s0h) : r.k0;
-    r.first = c == first_c;
     r.last = c == last_c;
     return r;
 }
 
-// LOCAL: the end-state pass of a time split (every chunk but the last runs
-// from zero, or the first from the carried state, and stores its end state;
-// no output).  Otherwise: the filter pass proper, each chunk starting from its
-// chained state.
+// A time split cuts the recurrence at absolute multiples of a chunk length lc.
+// Every chunk's samples run from its start state S, which k_chain forms from the
+// zero-start run of the chunk before, S' = a1^lc S + E.  Both runs of a chunk
+// in progress at a block's end are carried on, so where blocks begin changes no
+// result.
+//
+// LOCAL: the end-state pass, every chunk from zero (the chunk in progress from
+// its carried zero-start state); stores the end states, no output.  Otherwise
+// the filter pass, every chunk from its start state (the chunk in progress from
+// the carried state).
+//
+// Start state of a filter slot: y and the pending carry correction u = dC * (y
+// at the start of the current carry chunk), added to y at that chunk's end.  A
+// chunk starts on a carry-chunk boundary, so u = dC * y there.  The end-state
+// pass copies the carried state (y0, ys0) for the filter pass, whose last chunk
+// overwrites it.
+template <bool LOCAL>
+__device__ __forceinline__ void start_state(CBankDev* bd, int nchunk, int tc, int64_t g, const c32& d, c32& y, c32& u)
+{
+    if (nchunk > 1 && tc > 0) {
+        y = LOCAL ? c32{0.0f, 0.0f} : gmem(bd->schain)[(int64_t)tc * bd->n_slots + g];
+        u = c32{fmaf(d.x, y.x, -d.y * y.y), fmaf(d.x, y.y, d.y * y.x)};
+    } else if (LOCAL) {
+        gmem(bd->y0)[g] = gmem(bd->y)[g];
+        gmem(bd->ys0)[g] = gmem(bd->ys)[g];
+        y = gmem(bd->ey)[g];
+        u = gmem(bd->eu)[g];
+    } else {
+        y = gmem(nchunk > 1 ? bd->y0 : bd->y)[g];
+        u = gmem(nchunk > 1 ? bd->ys0 : bd->ys)[g];
+    }
+}
+
 template <int F, bool COMP, bool LOCAL>
 __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COMP)) k_filter(LaunchArgs args)
 {
@@ -405,11 +441,16 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
     const int L = blockDim.x;
     const int tid = threadIdx.x;
     const int nh = q.n >> h;
-    const int64_t s0 = LOCAL ? cmem(bd->clock)[0] : block_start(q, bd, sm);
-    if (!LOCAL && q.direct && li == 0) append_block(q, bd, s0);
+    // who stages the block: the staging launch, this launch, or (single rate,
+    // split in time) the end-state pass before it
+    const bool stages = q.direct == (LOCAL ? kDirectSplit : kDirect);
+    const int64_t s0 = q.direct == kDirect ? block_start(q, bd, sm)
+                       : LOCAL && stages   ? cmem(bd->clock)[1]
+                                           : cmem(bd->clock)[0];
+    if (stages && li == 0) append_block(q, bd, s0);
     const int64_t s0h = s0 >> h;
     const Chunk ch = chunk_range(tc, q.nchunk, s0h, nh, bd->lc[h]);
-    if (ch.k0 >= ch.k1 || (LOCAL && ch.last)) return;  // whole workgroup
+    if (ch.k0 >= ch.k1) return;  // whole workgroup
     const int64_t cmask = bd->C - 1;
     const int nrun = bd->nrun_max;
 
@@ -433,43 +474,17 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 
     float ar[F], ai[F], br[F], bi[F], dr[F], di[F], yr[F], yi[F], ur[F], ui[F];
     int dl[F];
-    // Start state: y and the pending carry correction u = dC * (y at the start
-    // of the current carry chunk), which is added to y at the chunk's end.
-    // The first chunk starts from the carried state; when the block has more
-    // than one chunk, the end-state pass saves that state (schain row of the
-    // first chunk, ys0) for the filter pass, whose last chunk overwrites the
-    // carried state while the first may still read it.  A later chunk starts
-    // from zero in the end-state pass and from its chained state in the
-    // filter pass; its start is a carry-chunk boundary, so u = dC * y there.
-    const c32* ysrc = bd->y;
-    const c32* yssrc = bd->ys;
-    if (!ch.first) ysrc = yssrc = bd->schain + (int64_t)tc * bd->n_slots;
-    else if (!LOCAL && !ch.last) {
-        ysrc = bd->schain + (int64_t)tc * bd->n_slots;
-        yssrc = bd->ys0;
-    }
-    const SPIIR_AS_GLOBAL c32* ysg = gmem(ysrc);
-    const SPIIR_AS_GLOBAL c32* yssg = gmem(yssrc);
 #pragma unroll
     for (int f = 0; f < F; ++f) {
         const int64_t g = wg.slot_base + (int64_t)f * L + tid;
-        c32 y = ysg[g], ys = yssg[g];
-        if (LOCAL && !ch.first) y = ys = c32{0.0f, 0.0f};
-        if (LOCAL && ch.first) {
-            gmem(bd->schain)[(int64_t)tc * bd->n_slots + g] = y;
-            gmem(bd->ys0)[g] = ys;
-        }
         const c32 a = cmem(bd->a)[g], b = cmem(bd->b)[g], d = cmem(bd->dc)[g];
+        c32 y, u;
+        start_state<LOCAL>(bd, q.nchunk, tc, g, d, y, u);
         ar[f] = a.x; ai[f] = a.y;
         br[f] = b.x; bi[f] = b.y;
         dr[f] = d.x; di[f] = d.y;
         yr[f] = y.x; yi[f] = y.y;
-        if (ch.first) {
-            ur[f] = ys.x; ui[f] = ys.y;
-        } else {
-            ur[f] = fmaf(d.x, y.x, -d.y * y.y);
-            ui[f] = fmaf(d.x, y.y, d.y * y.x);
-        }
+        ur[f] = u.x; ui[f] = u.y;
         dl[f] = cmem(bd->off)[g];
     }
     __syncthreads();
@@ -514,7 +529,7 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
         const int64_t origin = ((s0h + kb - wg.maxd - 1) >> 6) << 6;
         const int wn = (int)(s0h + kb + sub - origin);
         __syncthreads();
-        if (q.direct)
+        if (stages)
             stage_window(E0, two_copies ? E1 : nullptr, wn, [&](int i) {
                 const int64_t a = origin + i;  // (a past the block's end is not used)
                 const SPIIR_AS_CONST float* p = a < s0 ? ring + (a & mk) : xblk + min((int)(a - s0), q.n - 1);
@@ -647,7 +662,11 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
     if (LOCAL) {
         SPIIR_AS_GLOBAL c32* ue = gmem(bd->uend) + (int64_t)tc * bd->n_slots;
 #pragma unroll
-        for (int f = 0; f < F; ++f) ue[wg.slot_base + (int64_t)f * L + tid] = c32{yr[f], yi[f]};
+        for (int f = 0; f < F; ++f) {
+            const int64_t g = wg.slot_base + (int64_t)f * L + tid;
+            ue[g] = c32{yr[f], yi[f]};
+            if (ch.last) gmem(bd->euend)[g] = c32{ur[f], ui[f]};
+        }
         return;
     }
     if (!ch.last) return;  // only the block's last chunk carries its state on
@@ -716,11 +735,13 @@ __device__ __forceinline__ float split_sum(float (&tr)[NF], float (&ti)[NF])
     return s;
 }
 
-// Two samples of Eq. 7 (see one_step) with the pair sums returned.
-template <int X, int NF, bool SUM>
+// One sample of Eq. 7 (see one_step) with the pair sum returned; DUAL: the
+// zero-start run (er, ei) too.
+template <int X, int NF, bool SUM, bool DUAL>
 __device__ __forceinline__ void split_step(const float (&xv)[NF], float& out, const float (&ar)[NF],
                                            const float (&ai)[NF], const float (&br)[NF],
-                                           const float (&bi)[NF], float (&yr)[NF], float (&yi)[NF])
+                                           const float (&bi)[NF], float (&yr)[NF], float (&yi)[NF],
+                                           float (&er)[NF], float (&ei)[NF])
 {
     float tr[NF], ti[NF];
 #pragma unroll
@@ -730,6 +751,11 @@ __device__ __forceinline__ void split_step(const float (&xv)[NF], float& out, co
         const float ni = fmaf(ar[f], yi[f], fmaf(ai[f], yr[f], pi));
         yr[f] = nr; yi[f] = ni;
         tr[f] = nr; ti[f] = ni;
+        if (DUAL) {
+            const float mr = fmaf(ar[f], er[f], fmaf(-ai[f], ei[f], pr));
+            const float mi = fmaf(ar[f], ei[f], fmaf(ai[f], er[f], pi));
+            er[f] = mr; ei[f] = mi;
+        }
     }
     if (SUM) out = split_sum<X, NF>(tr, ti);
 }
@@ -745,7 +771,7 @@ constexpr int kAhead = 4;     // x pairs read ahead
 constexpr int kRunAhead = 8;  // run sums a level-2 task reads ahead
 
 
-template <int F, int X, bool COMP, bool LOCAL>
+template <int F, int X, bool COMP, bool LOCAL, bool DUAL>
 __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
 {
     constexpr int NF = F / X;
@@ -771,11 +797,16 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     const int ln = tid / X, part = tid % X;  // lane of the layout, thread of the lane
     const bool flip = part & 1;
     const int nh = q.n >> h;
-    const int64_t s0 = LOCAL ? cmem(bd->clock)[0] : block_start(q, bd, sm);
-    if (!LOCAL && q.direct && li == 0) append_block(q, bd, s0);
+    // who stages the block: the staging launch, this launch, or (single rate,
+    // split in time) the end-state pass before it
+    const bool stages = q.direct == (LOCAL ? kDirectSplit : kDirect);
+    const int64_t s0 = q.direct == kDirect ? block_start(q, bd, sm)
+                       : LOCAL && stages   ? cmem(bd->clock)[1]
+                                           : cmem(bd->clock)[0];
+    if (stages && li == 0) append_block(q, bd, s0);
     const int64_t s0h = s0 >> h;
     const Chunk ch = chunk_range(tc, q.nchunk, s0h, nh, bd->lc[h]);
-    if (ch.k0 >= ch.k1 || (LOCAL && ch.last)) return;  // whole workgroup
+    if (ch.k0 >= ch.k1) return;  // whole workgroup
     const int64_t cmask = bd->C - 1;
     const int nrun = bd->nrun_max;
 
@@ -798,44 +829,42 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     for (int i = tid; i < 2 * kTile * nrun; i += NT) l2buf[i] = c32{0.0f, 0.0f};
 
     float ar[NF], ai[NF], br[NF], bi[NF], dr[NF], di[NF], yr[NF], yi[NF], ur[NF], ui[NF];
+    float er[NF], ei[NF], eur[NF], eui[NF];  // DUAL: the zero-start run of the chunk in progress
     int dl[NF];
-    const c32* ysrc = bd->y;  // start states: as in k_filter
-    const c32* yssrc = bd->ys;
-    if (!ch.first) ysrc = yssrc = bd->schain + (int64_t)tc * bd->n_slots;
-    else if (!LOCAL && !ch.last) {
-        ysrc = bd->schain + (int64_t)tc * bd->n_slots;
-        yssrc = bd->ys0;
-    }
-    const SPIIR_AS_GLOBAL c32* ysg = gmem(ysrc);
-    const SPIIR_AS_GLOBAL c32* yssg = gmem(yssrc);
+    const bool dual = DUAL && q.dual;
+    const int lc = bd->lc[h];
+    const int to_boundary = dual ? lc - (int)(s0h % lc) : 0;  // samples to the end of the chunk in progress
     const int64_t slot0_ = wg.slot_base + (int64_t)part * NF * L + ln;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         const int64_t g = slot0_ + (int64_t)f * L;
-        c32 y = ysg[g], ys = yssg[g];
-        if (LOCAL && !ch.first) y = ys = c32{0.0f, 0.0f};
-        if (LOCAL && ch.first) {
-            gmem(bd->schain)[(int64_t)tc * bd->n_slots + g] = y;
-            gmem(bd->ys0)[g] = ys;
+        c32 a = cmem(bd->a)[g], b = cmem(bd->b)[g], d = cmem(bd->dc)[g], y, u;
+        start_state<LOCAL>(bd, q.nchunk, tc, g, d, y, u);
+        c32 e{0.0f, 0.0f}, eu{0.0f, 0.0f};
+        if (dual) {
+            if (to_boundary == lc) {  // the block starts a chunk
+                y = gmem(bd->s)[g];
+                u = c32{fmaf(d.x, y.x, -d.y * y.y), fmaf(d.x, y.y, d.y * y.x)};
+            }
+            e = gmem(bd->ey)[g];
+            eu = gmem(bd->eu)[g];
         }
-        c32 a = cmem(bd->a)[g], b = cmem(bd->b)[g], d = cmem(bd->dc)[g];
         if (flip) {
+            e = c32{e.y, e.x};
+            eu = c32{eu.y, eu.x};
             a.y = -a.y;
             d.y = -d.y;
             b = c32{b.y, b.x};
             y = c32{y.y, y.x};
-            ys = c32{ys.y, ys.x};
+            u = c32{u.y, u.x};
         }
         ar[f] = a.x; ai[f] = a.y;
         br[f] = b.x; bi[f] = b.y;
         dr[f] = d.x; di[f] = d.y;
         yr[f] = y.x; yi[f] = y.y;
-        if (ch.first) {
-            ur[f] = ys.x; ui[f] = ys.y;
-        } else {
-            ur[f] = fmaf(d.x, y.x, -d.y * y.y);
-            ui[f] = fmaf(d.x, y.y, d.y * y.x);
-        }
+        ur[f] = u.x; ui[f] = u.y;
+        er[f] = e.x; ei[f] = e.y;
+        eur[f] = eu.x; eui[f] = eu.y;
         dl[f] = cmem(bd->off)[g];
     }
     __syncthreads();
@@ -1007,14 +1036,47 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
                 if (X == 1) zp[1] = (float)si;
             }
     };
-    auto correct = [&](int64_t kend) {  // the carry correction, as in k_filter
-        if ((kend & cmask) != 0) return;
+    auto unflip = [&](float r, float i) { return flip ? c32{i, r} : c32{r, i}; };
+    int boundary = to_boundary;  // block sample where the chunk in progress ends (DUAL)
+    // after block sample kend - 1: the carry correction, as in k_filter; DUAL,
+    // at a chunk's end: the next one's start state (k_chain's arithmetic)
+    auto correct = [&](int kend) {
+        if (((s0h + kend) & cmask) != 0) return;
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             yr[f] += ur[f];
             yi[f] += ui[f];
             ur[f] = fmaf(dr[f], yr[f], -di[f] * yi[f]);
             ui[f] = fmaf(dr[f], yi[f], di[f] * yr[f]);
+            if (DUAL) {
+                er[f] += eur[f];
+                ei[f] += eui[f];
+                eur[f] = fmaf(dr[f], er[f], -di[f] * ei[f]);
+                eui[f] = fmaf(dr[f], ei[f], di[f] * er[f]);
+            }
+        }
+        if (!dual || kend != boundary) return;
+        boundary += lc;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const int64_t g = slot0_ + (int64_t)f * L;
+            c32 st = gmem(bd->s)[g], al = cmem(bd->al)[g], dl_ = cmem(bd->al)[bd->n_slots + g];
+            if (flip) {
+                st = c32{st.y, st.x};
+                al.y = -al.y;
+                dl_.y = -dl_.y;
+            }
+            const float ux = fmaf(dl_.x, st.x, fmaf(-dl_.y, st.y, er[f]));
+            const float uy = fmaf(dl_.x, st.y, fmaf(dl_.y, st.x, ei[f]));
+            st = c32{fmaf(al.x, st.x, fmaf(-al.y, st.y, ux)), fmaf(al.x, st.y, fmaf(al.y, st.x, uy))};
+            gmem(bd->s)[g] = unflip(st.x, st.y);
+            er[f] = ei[f] = eur[f] = eui[f] = 0.0f;
+            if (kend < nh) {
+                yr[f] = st.x;
+                yi[f] = st.y;
+                ur[f] = fmaf(dr[f], yr[f], -di[f] * yi[f]);
+                ui[f] = fmaf(dr[f], yi[f], di[f] * yr[f]);
+            }
         }
     };
     // the pipeline one step on, after tile (k, cnt)
@@ -1042,7 +1104,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         const int64_t origin = ((s0h + kb - wg.maxd - 1) >> 6) << 6;
         const int wn = (int)(s0h + kb + sub - origin);
         __syncthreads();
-        if (q.direct)
+        if (stages)
             stage_window(E0, two_copies ? E1 : nullptr, wn, [&](int i) {
                 const int64_t a = origin + i;  // (a past the block's end is not used)
                 const SPIIR_AS_CONST float* p = a < s0 ? ring + (a & mk) : xblk + min((int)(a - s0), q.n - 1);
@@ -1067,10 +1129,10 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
                     float xs[NF], o = 0.0f;
 #pragma unroll
                     for (int f = 0; f < NF; ++f) xs[f] = E0[rel0 + k + j - dl[f]];
-                    split_step<X, NF, !LOCAL>(xs, o, ar, ai, br, bi, yr, yi);
+                    split_step<X, NF, !LOCAL, DUAL>(xs, o, ar, ai, br, bi, yr, yi, er, ei);
                     if (!LOCAL && (j & (X - 1)) == px) pcol[2 * j] = o;
                 }
-                correct(s0h + k + cnt);
+                correct(k + cnt);
             }
             if (!LOCAL) advance(k, cnt);
         };
@@ -1111,8 +1173,10 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
                         xa[f] = xv[f][jj % kAhead].x;
                         xb[f] = xv[f][jj % kAhead].y;
                     }
-                    split_step<X, NF, !LOCAL>(xa, out[2 * jj], ar, ai, br, bi, yr, yi);
-                    split_step<X, NF, !LOCAL>(xb, out[2 * jj + 1], ar, ai, br, bi, yr, yi);
+                    split_step<X, NF, !LOCAL, DUAL>(xa, out[2 * jj], ar, ai, br, bi, yr, yi,
+                                                           er, ei);
+                    split_step<X, NF, !LOCAL, DUAL>(xb, out[2 * jj + 1], ar, ai, br, bi, yr, yi,
+                                                           er, ei);
                     if (!LOCAL) {  // after load1
                         if (X == 1) {
                             pcol[4 * jj] = out[2 * jj];
@@ -1134,7 +1198,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
                     level1(single_run);
                     if (duty) level2();
                 }
-                correct(s0h + k + kTile);
+                correct(k + kTile);
                 if (!LOCAL) advance(k, kTile);
             }
         };
@@ -1163,11 +1227,13 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         }
     }
 
-    auto unflip = [&](float r, float i) { return flip ? c32{i, r} : c32{r, i}; };
     if (LOCAL) {
         SPIIR_AS_GLOBAL c32* ue = gmem(bd->uend) + (int64_t)tc * bd->n_slots;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) ue[slot0_ + (int64_t)f * L] = unflip(yr[f], yi[f]);
+        for (int f = 0; f < NF; ++f) {
+            ue[slot0_ + (int64_t)f * L] = unflip(yr[f], yi[f]);
+            if (ch.last) gmem(bd->euend)[slot0_ + (int64_t)f * L] = unflip(ur[f], ui[f]);
+        }
         return;
     }
     if (!ch.last) return;  // only the block's last chunk carries its state on
@@ -1177,6 +1243,10 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         const int64_t g = slot0_ + (int64_t)f * L;
         gmem(bd->y)[g] = unflip(yr[f], yi[f]);
         gmem(bd->ys)[g] = unflip(ur[f], ui[f]);
+        if (dual) {
+            gmem(bd->ey)[g] = unflip(er[f], ei[f]);
+            gmem(bd->eu)[g] = unflip(eur[f], eui[f]);
+        }
         bad |= !(isfinite(yr[f]) && isfinite(yi[f]));
     }
     if (bad) {
@@ -1737,14 +1807,17 @@ __global__ void __launch_bounds__(kUpThreads, 4) k_upadd(LaunchArgs args)
 }
 
 // ---------------------------------------------------------------------------
-// Time split, middle pass: per filter slot, the start state of every chunk
-// after the first, S[c+1] = uend[c] + a1^lc S[c] with S[first+1] = uend[first]
-// (the first chunk's end state, which ran from the carried state).  The
-// product uses the same component formula as the recurrence, so it also holds
-// for the swapped form of odd lanes.  One thread per slot; request r owns
-// blocks [cum[r], cum[r+1]).
+// Time split, middle pass: per filter slot, the start state of every chunk of
+// the block, S[c+1] = a1^lc S[c] + uend[c] from the carried start of the first
+// one, and what is carried on: the start state of the chunk in progress at the
+// block's end and its zero-start state so far.  a1^lc is taken as fl32 plus
+// the rest, so that its rounding does not add up over a slow filter's many
+// chunks.  The product uses the same component formula as the recurrence, so it
+// also holds for the swapped form of odd lanes.  One thread per slot; request r
+// owns blocks [cum[r], cum[r+1]).
 // ---------------------------------------------------------------------------
 constexpr int kChainThreads = 256;
+constexpr int kChainAhead = 8;
 
 __global__ void __launch_bounds__(kChainThreads) k_chain(LaunchArgs args)
 {
@@ -1753,26 +1826,43 @@ __global__ void __launch_bounds__(kChainThreads) k_chain(LaunchArgs args)
     while (r + 1 < args.nreq && args.cum[r + 1] <= bid) ++r;
     const ReqArg& q = args.req[r];
     CBankDev* bd = cmem(q.bd);
+    const int64_t s0 = cmem(bd->clock)[0];
     const int64_t g = (int64_t)(bid - args.cum[r]) * kChainThreads + threadIdx.x;
+    if (q.direct == kDirectSplit && g == 0) gmem(bd->clock)[1] = s0 + q.n;
     if (g >= bd->n_slots) return;
     const int h = cmem(bd->wg)[g / ((int64_t)bd->F * bd->L)].band;
     const int nh = q.n >> h, lc = bd->lc[h];
-    const int64_t s0h = cmem(bd->clock)[0] >> h;
+    const int64_t s0h = s0 >> h, end = s0h + nh;
     const int64_t B = (s0h + lc - 1) / lc * lc;
     const int first_c = B == s0h ? 1 : 0;
-    const int last_c = s0h + nh - 1 < B ? 0 : 1 + (int)((s0h + nh - 1 - B) / lc);
+    const int last_c = end - 1 < B ? 0 : 1 + (int)((end - 1 - B) / lc);
     const int64_t ns = bd->n_slots;
     const SPIIR_AS_CONST c32* uend = cmem(bd->uend);
     SPIIR_AS_GLOBAL c32* schain = gmem(bd->schain);
-    c32 st = uend[first_c * ns + g];
-    const c32 al = cmem(bd->al)[g];
-    for (int c = first_c + 1; c <= last_c; ++c) {
-        schain[c * ns + g] = st;
-        if (c < last_c) {
-            const c32 u = uend[c * ns + g];
+    c32 st = gmem(bd->s)[g];
+    const c32 al = cmem(bd->al)[g], dl = cmem(bd->al)[ns + g];
+    const bool whole = end % lc == 0;  // the last chunk ends with the block
+    c32 u{0.0f, 0.0f};
+    // the end states are read kChainAhead at a time: one wait for as many chunks
+    for (int c0 = first_c; c0 <= last_c; c0 += kChainAhead) {
+        c32 ue[kChainAhead];
+#pragma unroll
+        for (int i = 0; i < kChainAhead; ++i) ue[i] = uend[min(c0 + i, last_c) * ns + g];
+#pragma unroll
+        for (int i = 0; i < kChainAhead; ++i) {
+            const int c = c0 + i;
+            if (c > last_c) break;
+            schain[c * ns + g] = st;
+            u = ue[i];
+            if (c == last_c && !whole) break;
+            u.x = fmaf(dl.x, st.x, fmaf(-dl.y, st.y, u.x));
+            u.y = fmaf(dl.x, st.y, fmaf(dl.y, st.x, u.y));
             st = c32{fmaf(al.x, st.x, fmaf(-al.y, st.y, u.x)), fmaf(al.x, st.y, fmaf(al.y, st.x, u.y))};
         }
     }
+    gmem(bd->s)[g] = st;
+    gmem(bd->ey)[g] = whole ? c32{0.0f, 0.0f} : u;
+    gmem(bd->eu)[g] = whole ? c32{0.0f, 0.0f} : gmem(bd->euend)[g];
 }
 
 int launch_chain(const LaunchArgs& a, int64_t nblocks, void* stream)
@@ -1815,18 +1905,19 @@ __global__ void k_prep(const c64* __restrict__ a, const c64* __restrict__ b, int
         }
     }
     const float alr = (float)al.x, ali = (float)al.y;
+    const float rlr = (float)(al.x - (double)alr), rli = (float)(al.y - (double)ali);
     if (i & 1) {
         // odd lane (slots of a workgroup are lane-contiguous and L is even):
         // tables for the swapped state (Im y, Re y)
         fa[i] = c32{ar, -ai};
         fb[i] = c32{(float)bv.y, (float)bv.x};
         fdc[i] = c32{dcr, -dci};
-        if (fal) fal[i] = c32{alr, -ali};
+        if (fal) fal[i] = c32{alr, -ali}, fal[n + i] = c32{rlr, -rli};
     } else {
         fa[i] = c32{ar, ai};
         fb[i] = c32{(float)bv.x, (float)bv.y};
         fdc[i] = c32{dcr, dci};
-        if (fal) fal[i] = c32{alr, ali};
+        if (fal) fal[i] = c32{alr, ali}, fal[n + i] = c32{rlr, rli};
     }
 }
 
@@ -1869,8 +1960,11 @@ template <int X>
 static int allow_pipe_lds_t()
 {
     int e = 0;
-    for (const void* k : {(const void*)k_filter_pipe<4, X, false, false>, (const void*)k_filter_pipe<4, X, true, false>,
-                          (const void*)k_filter_pipe<4, X, false, true>})
+    constexpr bool kDual = X > 1;
+    for (const void* k :
+         {(const void*)k_filter_pipe<4, X, false, false, false>, (const void*)k_filter_pipe<4, X, true, false, false>,
+          (const void*)k_filter_pipe<4, X, false, true, false>, (const void*)k_filter_pipe<4, X, false, false, kDual>,
+          (const void*)k_filter_pipe<4, X, true, false, kDual>})
         if (!e) e = (int)hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, filter_max_lds());
     return e;
 }
@@ -1935,28 +2029,35 @@ int launch_filter_local(int F, int precision, const LaunchArgs& a, int nblocks, 
     return launch_filter_any<true>(F, SPIIR_FP32, a, nblocks, L, lds_bytes, (hipStream_t)stream);
 }
 
-template <int X, bool LOCAL>
-static int launch_pipe_t(bool comp, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes, hipStream_t s)
+template <int X, bool COMP, bool LOCAL, bool DUAL>
+static int launch_pipe_t(const LaunchArgs& a, int nblocks, int lanes, int lds_bytes, hipStream_t s)
 {
-    if (comp && !LOCAL)
-        hipLaunchKernelGGL((k_filter_pipe<4, X, !LOCAL, LOCAL>), dim3(nblocks), dim3(lanes * X), lds_bytes, s, a);
-    else
-        hipLaunchKernelGGL((k_filter_pipe<4, X, false, LOCAL>), dim3(nblocks), dim3(lanes * X), lds_bytes, s, a);
+    hipLaunchKernelGGL((k_filter_pipe<4, X, COMP, LOCAL, DUAL>), dim3(nblocks), dim3(lanes * X), lds_bytes, s, a);
     return (int)hipGetLastError();
 }
 
-int launch_filter_pipe(int X, bool local, int precision, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
+template <int X>
+static int launch_pipe_x(PipeMode mode, bool comp, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
+                         hipStream_t s)
+{
+    constexpr bool kDual = X > 1;  // one thread per lane has no registers left for it
+    if (mode == PipeMode::kLocal) return launch_pipe_t<X, false, true, false>(a, nblocks, lanes, lds_bytes, s);
+    if (mode == PipeMode::kDual)
+        return !kDual ? (int)hipErrorInvalidValue
+               : comp ? launch_pipe_t<X, true, false, kDual>(a, nblocks, lanes, lds_bytes, s)
+                      : launch_pipe_t<X, false, false, kDual>(a, nblocks, lanes, lds_bytes, s);
+    return comp ? launch_pipe_t<X, true, false, false>(a, nblocks, lanes, lds_bytes, s)
+                : launch_pipe_t<X, false, false, false>(a, nblocks, lanes, lds_bytes, s);
+}
+
+int launch_filter_pipe(int X, PipeMode mode, int precision, const LaunchArgs& a, int nblocks, int lanes, int lds_bytes,
                        void* stream)
 {
-    const bool comp = !local && precision == SPIIR_FP32_COMPENSATED;
+    const bool comp = precision == SPIIR_FP32_COMPENSATED;
     hipStream_t s = (hipStream_t)stream;
-    if (local)
-        return X == 1 ? launch_pipe_t<1, true>(comp, a, nblocks, lanes, lds_bytes, s)
-             : X == 2 ? launch_pipe_t<2, true>(comp, a, nblocks, lanes, lds_bytes, s)
-                      : launch_pipe_t<4, true>(comp, a, nblocks, lanes, lds_bytes, s);
-    return X == 1 ? launch_pipe_t<1, false>(comp, a, nblocks, lanes, lds_bytes, s)
-         : X == 2 ? launch_pipe_t<2, false>(comp, a, nblocks, lanes, lds_bytes, s)
-                  : launch_pipe_t<4, false>(comp, a, nblocks, lanes, lds_bytes, s);
+    return X == 1   ? launch_pipe_x<1>(mode, comp, a, nblocks, lanes, lds_bytes, s)
+           : X == 2 ? launch_pipe_x<2>(mode, comp, a, nblocks, lanes, lds_bytes, s)
+                    : launch_pipe_x<4>(mode, comp, a, nblocks, lanes, lds_bytes, s);
 }
 
 int launch_filter_mfma(const LaunchArgs& a, int nblocks, int lds_bytes, void* stream)

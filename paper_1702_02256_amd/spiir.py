@@ -11,6 +11,7 @@ from __future__ import annotations
 import ctypes as C
 import os
 import re
+import struct
 
 import numpy as np
 
@@ -399,6 +400,15 @@ def _torch_hip_first():
         torch.cuda.init()
 
 
+def _blob_bytes(blob: bytes) -> int:
+    """Length of a state blob by its header (0 if it has none)."""
+    if len(blob) < 128:
+        return 0
+    version, T = struct.unpack_from("<Ii", blob, 4)
+    slots, ring, _, hist = struct.unpack_from("<4q", blob, 32)
+    return 128 + slots * (16 if version == 3 else 40) + 4 * ring + 8 * hist + 4 * T
+
+
 class Bank:
     """One template bank bound to one input stream (owns its device memory)."""
 
@@ -486,8 +496,9 @@ class Bank:
         return buf.raw
 
     def load_state(self, blob: bytes, stream=None) -> None:
-        # the library reads state_size() bytes: a blob of another length is refused here
-        if len(blob) != self.state_size():
+        # the library reads what the header announces: a blob of another length
+        # is refused here (blobs without a time split's state are shorter)
+        if len(blob) != _blob_bytes(blob):
             raise SpiirError(SPIIR_EINVAL, "spiir_load_state")
         buf = C.create_string_buffer(bytes(blob), len(blob))
         _check(self._lib.spiir_load_state(self._h, buf, _stream_handle(stream)), "spiir_load_state")
