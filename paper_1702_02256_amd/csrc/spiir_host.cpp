@@ -471,7 +471,7 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
     p.nrun_max |= 1;
     p.lds_filter = p.copies * p.xcap * 4 + (L / 2) * (kTile + 1) * 8 + 2 * kTile * p.nrun_max * 8 + p.npiece_max * 8 +
                    L * 4 + p.npiece_max * 8;
-    p.lds_stage = ((p.td - 1) + p.mb_inner + (p.td - 1) + p.mb_inner / 2 + p.td) * 4;
+    p.lds_stage = (((p.td + p.mb_inner) & ~1) + ((p.td + p.mb_inner / 2) & ~1) + p.td) * 4;
     p.lds_up = (2 * (p.hu_len + p.mb_inner / 2) + std::max(p.H - 2, 0) * p.hu_len) * 8 + p.tu * 4;
     if (p.lds_stage > kMaxLds || p.lds_up > kMaxLds) return SPIIR_EINVAL;
     if (p.lds_filter > kMaxLds) return kNoFit;
@@ -788,7 +788,7 @@ int make_plan_mfma(const spiir_bank_desc* d, Plan& p)
     }
     p.band_wg0[1] = (int)p.wg.size();
     p.lds_filter = 4 * p.xcap * 2 + 2 * 16 * (kMfmaSlots + 4) * 4 + 4 * 16 * 17 * 4;
-    p.lds_stage = ((p.td - 1) + p.mb_inner + (p.td - 1) + p.mb_inner / 2 + p.td) * 4;
+    p.lds_stage = (((p.td + p.mb_inner) & ~1) + ((p.td + p.mb_inner / 2) & ~1) + p.td) * 4;
     p.lds_up = (2 * (p.hu_len + p.mb_inner / 2)) * 8 + p.tu * 4;
     if (p.lds_filter > kMaxLds) return SPIIR_EINVAL;
     size_t fp = 0;

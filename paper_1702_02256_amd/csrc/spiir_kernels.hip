@@ -49,6 +49,7 @@ __device__ __forceinline__ const SPIIR_AS_CONST T* cmem(const T* p)
     return (const SPIIR_AS_CONST T*)p;
 }
 typedef const SPIIR_AS_CONST BankDev CBankDev;
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
 
 // Waits for the wave's global loads (vmcnt 0).  Before a loop that stores: a
 // load whose wait the compiler cannot place on every path costs a wait in the
@@ -90,73 +91,92 @@ __device__ __forceinline__ int64_t block_start(const ReqArg& q, CBankDev* bd, fl
 
 // ---------------------------------------------------------------------------
 // Input staging and the downsample cascade (one workgroup per request).
+//
+// One workgroup walks the bands in turn, so its latency is what it costs: the
+// block and every band's history are read before the first band (one wait each
+// where each band had its own), and the common 32-tap decimator reads its
+// window as 16 aligned pairs: 4096 samples, 7 bands 15.5 -> 11 us.
+// LDS: cur [td-1 + max_block] | nxt [td-1 + max_block/2] | taps [td], each from an
+// even word.
+// ---------------------------------------------------------------------------
 constexpr int kStageThreads = 1024;
 constexpr int kStageFastTaps = 32;  // decimator length with an unrolled path
-// LDS: cur [td-1 + max_block] | nxt [td-1 + max_block/2] | taps [td]
-// ---------------------------------------------------------------------------
+constexpr int kStageSamples = kInnerBlock / kStageThreads;  // block samples per thread
+
 __global__ void __launch_bounds__(kStageThreads) k_stage(LaunchArgs args)
 {
     extern __shared__ float sm[];
-    __shared__ long long s_base;
     const ReqArg& q = args.req[blockIdx.x];
     if (q.direct) return;
     CBankDev* bd = cmem(q.bd);
     SPIIR_AS_GLOBAL int64_t* clock = gmem(bd->clock);
-    const SPIIR_AS_GLOBAL float* x = gmem(q.x);
-    const int n = q.n;
-    if (threadIdx.x == 0) s_base = clock[1];
-    __syncthreads();
-    const int64_t s0 = s_base;
-    if (threadIdx.x == 0) {
-        clock[0] = s0;      // read by the filter kernel that follows
-        clock[1] = s0 + n;
+    const SPIIR_AS_CONST float* x = cmem(q.x);
+    const int n = q.n, tid = threadIdx.x;
+    float xv[kStageSamples];
+#pragma unroll
+    for (int u = 0; u < kStageSamples; ++u) {
+        const int i = tid + u * kStageThreads;
+        xv[u] = i < n ? x[i] : 0.0f;
     }
+    const int64_t s0 = clock[1];
     const int H = bd->H;
     SPIIR_AS_GLOBAL float* rings = gmem(bd->rings);
     SPIIR_AS_GLOBAL float* ring0 = rings + bd->ring_off[0];
     const int64_t m0 = bd->ring_mask[0];
-    if (H == 1) {
-        for (int i = threadIdx.x; i < n; i += blockDim.x) ring0[(s0 + i) & m0] = x[i];
-        return;
-    }
 
     const int td = bd->td;
-    const int hl = td - 1;
+    const int hl = td - 1;  // at most kStageThreads: one history sample per thread and band
     const SPIIR_AS_CONST float* tap = cmem(bd->hd);
     float* cur = sm;
-    float* nxt = sm + hl + bd->max_block;
-    float* hd = nxt + hl + bd->max_block / 2;
-    for (int i = threadIdx.x; i < td; i += blockDim.x) hd[i] = cmem(bd->hd)[i];
-    for (int i = threadIdx.x; i < hl; i += blockDim.x) cur[i] = ring0[(s0 - hl + i) & m0];
+    float* nxt = sm + ((hl + bd->max_block + 1) & ~1);
+    float* hd = nxt + ((hl + bd->max_block / 2 + 1) & ~1);
+    float hist[kMaxBands] = {};
+#pragma unroll
+    for (int h = 0; h < kMaxBands - 1; ++h)
+        if (h < H - 1 && tid < hl) hist[h] = rings[bd->ring_off[h] + (((s0 >> h) - hl + tid) & bd->ring_mask[h])];
+    if (H > 1 && td != kStageFastTaps)
+        for (int i = tid; i < td; i += kStageThreads) hd[i] = tap[i];
     // the block goes to the band-0 ring and to LDS (the ring slots of the
-    // history read above are not among the ones written here)
-    for (int i = threadIdx.x; i < n; i += blockDim.x) {
-        const float v = x[i];
-        ring0[(s0 + i) & m0] = v;
-        cur[hl + i] = v;
+    // histories read above are not among the ones written here)
+#pragma unroll
+    for (int u = 0; u < kStageSamples; ++u) {
+        const int i = tid + u * kStageThreads;
+        if (i >= n) break;
+        ring0[(s0 + i) & m0] = xv[u];
+        if (H > 1) cur[hl + i] = xv[u];
     }
+    if (H > 1 && tid < hl) cur[tid] = hist[0];
     __syncthreads();
+    if (tid == 0) {
+        clock[0] = s0;  // read by the filter kernel that follows
+        clock[1] = s0 + n;
+    }
 
-    for (int h = 1; h < H; ++h) {
+#pragma unroll
+    for (int h = 1; h < kMaxBands; ++h) {
+        if (h >= H) break;
         const int nh = n >> h;
         const int64_t s0h = s0 >> h;
         SPIIR_AS_GLOBAL float* ring = rings + bd->ring_off[h];
         const int64_t mk = bd->ring_mask[h];
-        if (h < H - 1)
-            for (int i = threadIdx.x; i < hl; i += blockDim.x) nxt[i] = ring[(s0h - hl + i) & mk];
-        for (int m = threadIdx.x; m < nh; m += blockDim.x) {
+        if (h < H - 1 && tid < hl) nxt[tid] = hist[h];
+        for (int m = tid; m < nh; m += kStageThreads) {
             // x_h[m] = sum_j h_d[j] x_{h-1}[2m - j]; cur[hl + i] holds x_{h-1} at block offset i
-            const float* src = cur + hl + 2 * m;
             float s = 0.0f;
             if (td == kStageFastTaps) {
-                // the common 32-tap decimator: taps as scalar loads, the window read
-                // first, then the multiply-adds in the same order as the loop below
-                float w[kStageFastTaps];
+                // taps as scalar loads, the window (from the even word 2m) first, then
+                // the multiply-adds in the same order as the loop below
+                f32x2_t w[kStageFastTaps / 2];
+                const f32x2_t* src = reinterpret_cast<const f32x2_t*>(cur + 2 * m);
 #pragma unroll
-                for (int j = 0; j < kStageFastTaps; ++j) w[j] = src[-j];
+                for (int j = 0; j < kStageFastTaps / 2; ++j) w[j] = src[j];
 #pragma unroll
-                for (int j = 0; j < kStageFastTaps; ++j) s = fmaf(tap[j], w[j], s);
+                for (int j = 0; j < kStageFastTaps; ++j) {
+                    const int i = kStageFastTaps - 1 - j;
+                    s = fmaf(tap[j], i & 1 ? w[i / 2].y : w[i / 2].x, s);
+                }
             } else {
+                const float* src = cur + hl + 2 * m;
                 for (int j = 0; j < td; ++j) s = fmaf(hd[j], src[-j], s);
             }
             nxt[hl + m] = s;
@@ -292,7 +312,6 @@ __device__ __forceinline__ void one_step(const float (&xv)[F], float* __restrict
 // barrier still lets the next step's loads be issued during this step's
 // arithmetic.  The restrict qualifiers tell the compiler that the
 // partial-sum stores never alias the window.
-typedef float f32x2_t __attribute__((ext_vector_type(2)));
 template <int F, bool SUM>
 __device__ __forceinline__ void tile_full(const f32x2_t* const (&xp)[F], float* __restrict__ pcol,
                                           const float (&ar)[F],
