@@ -642,13 +642,14 @@ int auto_time_chunks(const Plan& p)
 
 // Time chunks of a bank that asks for none and leaves the launch shape to the
 // library.  The split adds an end-state pass, about half as much work again, so
-// it is kept to banks of which even the largest batch cannot be slowed down by
-// it much: SPIIR_MAX_BATCH of them make at most one workgroup of 256 lanes per
-// compute unit, as long as their longest.  Measured at that limit (45 templates, 5
-// bands, max_block 4096), us per call not split / split: blocks of 4096, 1024,
-// 256, 64 samples alone 349 / 90, 101 / 66, 55 / 55, 30 / 32, in a batch of 16 banks
-// 619 / 551, 225 / 232, 128 / 144, 105 / 124; one template of 128 filters, 4096
-// samples 151 / 37.
+// it is kept to small banks: SPIIR_MAX_BATCH of them make at most one workgroup
+// of 256 lanes per compute unit, as long as their longest.  It pays for long
+// blocks of few banks and costs for short ones and full batches.  Measured near
+// that limit (45 templates, 5 bands, max_block 4096), us per call not split /
+// split, blocks of 64, 256, 1024, 4096 samples: one bank 29 / 33, 45 / 55,
+// 108 / 66, 369 / 90; 16 banks 118 / 125, 132 / 146, 200 / 234, 462 / 553.  Far
+// below it (one template of 128 filters a band, 7 bands): one bank 27 / 28,
+// 33 / 34, 58 / 49, 171 / 56; 16 banks 96 / 97, 102 / 105, 129 / 124, 243 / 147.
 int small_bank_chunks(const Plan& p)
 {
     int64_t work = 0, longest = 0;
