@@ -118,9 +118,12 @@ enum {
  *                         filter pass runs every chunk from its start state.
  *                         Results differ from an unsplit bank's by rounding
  *                         only; where blocks begin changes no bit of them,
- *                         split or not.  The library splits very small banks
+ *                         split or not.  The library may run a bank in another
+ *                         number of chunks than P, or unsplit, where that is
+ *                         faster; spiir_plan reports P.  It splits very small banks
  *                         by itself when neither this, filters_per_lane nor
- *                         waves_per_group is given (spiir_plan then still
+ *                         waves_per_group is given and max_block is at least
+ *                         512 (spiir_plan then still
  *                         reports 1; the footprint and the state include the
  *                         split's arrays).
  *   window_copies         1 or 2; 0 = chosen by the library.  The filter

@@ -640,6 +640,48 @@ int auto_time_chunks(const Plan& p)
     return P;
 }
 
+// The chunks a split asked for in P is run in.  The pipelined kernel on whole
+// blocks beats a split in two (whose end-state pass is as long as the half block
+// it saves), any split of short blocks, and some in four; eight often beat four.
+// Measured, us per call, compensated, whole / 4 / 8 chunks: 512 single-rate
+// templates of 300 filters, blocks of 512, 1024, 2048, 4096 samples 61 / 69 / -,
+// 104 / 105 / 108, 193 / 178 / 168, 371 / 316 / 282; 512 templates in 3 bands
+// 68 / 66 / -, 113 / 97 / 98, 206 / 149 / 137, 390 / 240 / 221; in 7 bands
+// 74 / 98 / -, 117 / 126 / 138, 209 / 193 / 206, 395 / 317 / 331: eight win up to
+// about 5/8 of a round of the longest workgroups (152, 144 of them; 172 lose).
+// Whole / AUTO at 256 samples 36 to 48 / 49 to 59; at 448 and 480 (P = 32) 68 / 48
+// and 60 / 46.  In two, 700
+// templates of 1, 3 (1024 templates) and 7 bands, 4096 samples: 374, 396, 399
+// whole, 520, 546, 544 split.  A single band of more than one workgroup per
+// compute unit leaves a last round nearly empty, which eight chunks fill: 1024
+// single-rate templates, 2048 and 4096 samples 298 / 279 / 281, 575 / 520 / 512.
+// Launches that the pipelined kernel cannot take keep P.
+void set_chunks_run(Plan& p)
+{
+    const int P = p.P;
+    if (P < 2 || p.F != 4 || 2 * p.lanes_used > kPipeThreads) return;
+    int longest = 0, bands_used = 0;
+    int64_t work = 0;
+    for (int h = p.H - 1; h >= 0; --h)
+        if (p.band_wg0[h + 1] > p.band_wg0[h]) {
+            longest = std::max(p.mb_inner >> h, 1);
+            work += (int64_t)(p.band_wg0[h + 1] - p.band_wg0[h]) * longest;
+            ++bands_used;
+        }
+    int run = P;
+    if (longest <= kDualSamples)
+        run = 1;
+    else if (P == 2)
+        run = bands_used == 1 && (int)p.wg.size() > kComputeUnits && longest >= 2048 ? 8 : 1;
+    else if (P == 4 && longest >= 2048)
+        run = 8 * work <= 5 * longest * kComputeUnits ? 8 : 4;
+    else if (P == 4 && longest < 1024)
+        run = 4 * work > longest * kComputeUnits ? 1 : 4;
+    p.footprint -= split_bytes(p);
+    set_chunks(p, run);  // p.time_chunks, the P reported, stays
+    p.footprint += split_bytes(p);
+}
+
 // Time chunks of a bank that asks for none and leaves the launch shape to the
 // library.  The split adds an end-state pass, about half as much work again, so
 // it is kept to small banks: SPIIR_MAX_BATCH of them make at most one workgroup
@@ -650,6 +692,8 @@ int auto_time_chunks(const Plan& p)
 // 108 / 66, 369 / 90; 16 banks 118 / 125, 132 / 146, 200 / 234, 462 / 553.  Far
 // below it (one template of 128 filters a band, 7 bands): one bank 27 / 28,
 // 33 / 34, 58 / 49, 171 / 56; 16 banks 96 / 97, 102 / 105, 129 / 124, 243 / 147.
+// Banks for blocks under 512 samples never gain: 12 single-rate templates of 300
+// filters, max_block 256 and 512, 37 / 49 and 57 / 39.
 int small_bank_chunks(const Plan& p)
 {
     int64_t work = 0, longest = 0;
@@ -658,7 +702,7 @@ int small_bank_chunks(const Plan& p)
         work += nh;
         longest = std::max(longest, nh);
     }
-    if (work == 0 || work * p.L * SPIIR_MAX_BATCH > longest * 256 * kComputeUnits) return 1;
+    if (work == 0 || longest < 512 || work * p.L * SPIIR_MAX_BATCH > longest * 256 * kComputeUnits) return 1;
     int P = 1;
     while (P < 16 && longest >= 2 * P * 64) P *= 2;  // chunks of 64 samples or more
     return P;
@@ -813,7 +857,8 @@ int make_plan(const spiir_bank_desc* d, Plan& p)
     if (d && d->engine == SPIIR_ENGINE_MFMA) return make_plan_mfma(d, p);
     if (!d || d->time_chunks != SPIIR_TIME_CHUNKS_AUTO) {
         const int rc = make_plan_fixed(d, p);
-        if (rc == SPIIR_OK && p.P == 1 && !d->filters_per_lane && !d->waves_per_group) {
+        if (rc == SPIIR_OK && p.P > 1) set_chunks_run(p);
+        else if (rc == SPIIR_OK && !d->filters_per_lane && !d->waves_per_group) {
             const int P = small_bank_chunks(p);
             if (P > 1) {
                 set_chunks(p, P);
@@ -832,7 +877,9 @@ int make_plan(const spiir_bank_desc* d, Plan& p)
     d1.filters_per_lane = p.F;
     d1.waves_per_group = p.W;
     d1.window_copies = p.copies;
-    return make_plan_fixed(&d1, p);
+    rc = make_plan_fixed(&d1, p);
+    if (rc == SPIIR_OK) set_chunks_run(p);
+    return rc;
 }
 
 // ---------------------------------------------------------------- profiling
@@ -918,7 +965,7 @@ void free_bank(spiir_bank* b)
     if (!b) return;
     void* ptrs[] = {b->a,     b->b,     b->dc, b->y,  b->ys, b->off, b->wg,     b->piece, b->seg,
                     b->lane_meta, b->rings, b->hd, b->hu, b->zw, b->uphist, b->flags, b->clock, b->al, b->uend, b->schain,
-                    b->s, b->ey, b->eu, b->y0, b->ys0, b->euend,
+                    b->s,  // with ey, eu, euend, y0, ys0
                     b->kc, b->pw, b->bd};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -935,7 +982,7 @@ int zero_state(spiir_bank* b, hipStream_t s)
     if (p.P > 1) {
         // uend and euend too: lanes of padding that a launch leaves out never
         // write theirs, and k_chain reads every slot's
-        for (c32* a : {b->s, b->ey, b->eu, b->euend}) e |= launch_fill(a, p.n_slots * (int64_t)sizeof(c32), s);
+        e |= launch_fill(b->s, 4 * p.n_slots * (int64_t)sizeof(c32), s);  // s, ey, eu, euend
         e |= launch_fill(b->uend, (p.P + 1) * p.n_slots * (int64_t)sizeof(c32), s);
     }
     e |= launch_fill(b->rings, p.ring_total * (int64_t)sizeof(float), s);
@@ -1391,8 +1438,12 @@ static bool alloc_bank(spiir_bank* b)
         ok &= dalloc(&b->al, 2 * (size_t)p.n_slots) == hipSuccess;
         ok &= dalloc(&b->uend, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
         ok &= dalloc(&b->schain, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
-        for (c32** a : {&b->s, &b->ey, &b->eu, &b->y0, &b->ys0, &b->euend})
-            ok &= dalloc(a, p.n_slots) == hipSuccess;
+        // one allocation: s, ey, eu, euend, then y0, ys0
+        ok &= dalloc(&b->s, 6 * (size_t)p.n_slots) == hipSuccess;
+        if (b->s) {
+            c32* next = b->s;
+            for (c32** a : {&b->ey, &b->eu, &b->euend, &b->y0, &b->ys0}) *a = next += p.n_slots;
+        }
     }
     if (p.engine == SPIIR_ENGINE_MFMA) {
         ok &= dalloc(&b->kc, (size_t)p.n_slots * kMfmaT) == hipSuccess;
