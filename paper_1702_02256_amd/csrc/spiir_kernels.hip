@@ -507,6 +507,9 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
         ur[f] = u.x; ui[f] = u.y;
         dl[f] = cmem(bd->off)[g];
     }
+    // without it a lone workgroup of 512 lanes waits in its tile loop: 15 templates, 7
+    // bands, 3 streams of up to 14720 samples 2934 us, with it 2742
+    wait_loads();
     __syncthreads();
 
     // level-1 role: sample row j1 of the 16-lane group q1; runs end where endmask
