@@ -690,7 +690,7 @@ void set_chunks_run(Plan& p)
 // that limit (45 templates, 5 bands, max_block 4096), us per call not split /
 // split, blocks of 64, 256, 1024, 4096 samples: one bank 29 / 33, 45 / 55,
 // 108 / 66, 369 / 90; 16 banks 118 / 125, 132 / 146, 200 / 234, 462 / 553.  Far
-// below it (one template of 128 filters a band, 7 bands): one bank 27 / 28,
+// below it (one template in 7 bands): one bank 27 / 28,
 // 33 / 34, 58 / 49, 171 / 56; 16 banks 96 / 97, 102 / 105, 129 / 124, 243 / 147.
 // Banks for blocks under 512 samples never gain: 12 single-rate templates of 300
 // filters, max_block 256 and 512, 37 / 49 and 57 / 39.

@@ -5,6 +5,9 @@
 //             stream, writing every band's new samples to its ring;
 //   k_filter  the filter bank: Eq. 7 per filter with the state in VGPRs,
 //             Eq. 8 as a deterministic two-level LDS reduction per piece;
+//   k_filter_pipe  the same with the same bits for launches that leave the
+//             compute units short of waves;
+//   k_chain   chunk start states of a bank split in time;
 //   k_upadd   per template: sum a band's pieces, add the x2 upsampled lower
 //             band (§2.2, Fig. "multi"), lowest band first, write z;
 //   k_prep    FP64 precompute of the carry corrections a1^C - fl32(a1)^C;
