@@ -1097,12 +1097,18 @@ const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 // samples 39 / 44, 64 samples of 4 banks of 60 multi-rate templates 47 / 50 (X = 2),
 // of 16 such banks 110 / 134 (X = 1; 256 samples 139 / 144); 512 lanes leave no room for more threads, and
 // X = 1 there gains nothing (530 / 562; 1024 single-rate templates 301 / 303).
-int pipe_threads(int F, int lanes, int longest, double rounds)
+// Short runs of many workgroups lose too, each of which pays for its start:
+// more than two per compute unit need 32 tiles.  192, 256, 512 samples, k_filter /
+// X = 2: 833 workgroups (700 templates, 7 bands) 53 / 64, 61 / 68, 93 / 90; 609 (512
+// templates) 51 / 53, 59 / 58, 91 / 74; 364 (1024 templates, 3 bands) 48 / 43, 57 / 48,
+// 93 / 72; 208 (700 single-rate templates) 41 / 36, 49 / 41, 82 / 63.
+int pipe_threads(int F, int lanes, int longest, double rounds, int64_t groups)
 {
     const double g = rounds * lanes / (256.0 * kComputeUnits);
     if (F != 4 || 2 * lanes > kPipeThreads || g > 2.0) return 0;
     const int x = g > 1.0 ? 1 : 4 * lanes <= kPipeThreads ? 4 : 2;
-    return longest >= (x == 1 ? 32 : x == 2 ? 8 : 4) * kTile ? x : 0;
+    const bool many = groups > 2 * kComputeUnits;
+    return longest >= (x == 1 || many ? 32 : x == 2 ? 8 : 4) * kTile ? x : 0;
 }
 
 // Kernels of one batch on `s`: per inner chunk of at most kInnerBlock base-rate
@@ -1168,7 +1174,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         const Shape* const shapes_end = shape_buf + nshape;
         // how full a shape's launch over the requests of X makes the device (pipe_threads)
         auto threads_of = [&](const Shape& sh, const LaunchArgs& X, int* lanes_out) {
-            int64_t work = 0;  // samples of all workgroups, and of the longest
+            int64_t work = 0, groups = 0;  // samples of all workgroups, and of the longest
             int longest = 1, lanes = 64;
             bool dual = false;
             for (int k = 0; k < X.nreq; ++k) {
@@ -1180,11 +1186,13 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                     const int nwg = p.band_wg0[h + 1] - p.band_wg0[h], nh = X.req[k].n >> h;
                     if (nwg == 0) continue;
                     work += (int64_t)nwg * nh;
+                    if (X.req[k].nchunk == 1) groups += nwg;
                     longest = std::max(longest, X.req[k].nchunk > 1 ? std::min(nh, p.lc[h]) : nh);
                 }
             }
             if (lanes_out) *lanes_out = lanes;
-            return pipe_threads(sh.F, lanes, dual ? std::max(longest, 8 * kTile) : longest, (double)work / longest);
+            return pipe_threads(sh.F, lanes, dual ? std::max(longest, 8 * kTile) : longest, (double)work / longest,
+                                dual ? 0 : groups);
         };
         // A short block of a bank split in time (two chunks) runs in one launch,
         // its chunks in turn in one workgroup that carries both runs, where
