@@ -973,18 +973,23 @@ void free_bank(spiir_bank* b)
     delete b;
 }
 
+// Zero chunk end states: lanes of padding that a launch leaves out never write
+// theirs, and k_chain reads every slot's.
+int clear_end_states(spiir_bank* b, hipStream_t s)
+{
+    const Plan& p = b->plan;
+    if (p.P <= 1) return 0;
+    return launch_fill(b->euend, p.n_slots * (int64_t)sizeof(c32), s) |
+           launch_fill(b->uend, (p.P + 1) * p.n_slots * (int64_t)sizeof(c32), s);
+}
+
 int zero_state(spiir_bank* b, hipStream_t s)
 {
     const Plan& p = b->plan;
-    int e = 0;
+    int e = clear_end_states(b, s);
     e |= launch_fill(b->y, p.n_slots * (int64_t)sizeof(c32), s);
     e |= launch_fill(b->ys, p.n_slots * (int64_t)sizeof(c32), s);
-    if (p.P > 1) {
-        // uend and euend too: lanes of padding that a launch leaves out never
-        // write theirs, and k_chain reads every slot's
-        e |= launch_fill(b->s, 4 * p.n_slots * (int64_t)sizeof(c32), s);  // s, ey, eu, euend
-        e |= launch_fill(b->uend, (p.P + 1) * p.n_slots * (int64_t)sizeof(c32), s);
-    }
+    if (p.P > 1) e |= launch_fill(b->s, 3 * p.n_slots * (int64_t)sizeof(c32), s);  // s, ey, eu
     e |= launch_fill(b->rings, p.ring_total * (int64_t)sizeof(float), s);
     e |= launch_fill(b->uphist, (int64_t)p.T * p.H * p.hu_len * (int64_t)sizeof(c32), s);
     e |= launch_fill(b->flags, (int64_t)p.T * (int64_t)sizeof(int32_t), s);
@@ -1916,7 +1921,7 @@ int spiir_load_state(spiir_bank* b, const void* host_buf, void* stream)
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const char* o = (const char*)host_buf + kStateHeaderBytes;
-    hipError_t e = hipSuccess;
+    hipError_t e = (hipError_t)clear_end_states(b, s);
     auto upl = [&](void* dst, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, o, bytes, hipMemcpyHostToDevice, s);
         o += bytes;
