@@ -103,6 +103,14 @@ void set_chunks(Plan& p, int P)
     }
 }
 
+// Runs a planned bank in P chunks (p.time_chunks, the P reported, stays).
+void set_run(Plan& p, int P)
+{
+    p.footprint -= split_bytes(p);
+    set_chunks(p, P);
+    p.footprint += split_bytes(p);
+}
+
 // Chunks of band h that a request can meet (workgroups per filter workgroup of the
 // plan in its launch).
 int chunk_slots(const Plan& p, int h, const ReqArg& q)
@@ -656,10 +664,10 @@ int auto_time_chunks(const Plan& p)
 // compute unit leaves a last round nearly empty, which eight chunks fill: 1024
 // single-rate templates, 2048 and 4096 samples 298 / 279 / 281, 575 / 520 / 512.
 // Launches that the pipelined kernel cannot take keep P.
-void set_chunks_run(Plan& p)
+int chunks_run(const Plan& p)
 {
     const int P = p.P;
-    if (P < 2 || p.F != 4 || 2 * p.lanes_used > kPipeThreads) return;
+    if (P < 2 || p.F != 4 || 2 * p.lanes_used > kPipeThreads) return P;
     int longest = 0, bands_used = 0;
     int64_t work = 0;
     for (int h = p.H - 1; h >= 0; --h)
@@ -677,9 +685,7 @@ void set_chunks_run(Plan& p)
         run = 8 * work <= 5 * longest * kComputeUnits ? 8 : 4;
     else if (P == 4 && longest < 1024)
         run = 4 * work > longest * kComputeUnits ? 1 : 4;
-    p.footprint -= split_bytes(p);
-    set_chunks(p, run);  // p.time_chunks, the P reported, stays
-    p.footprint += split_bytes(p);
+    return run;
 }
 
 // Time chunks of a bank that asks for none and leaves the launch shape to the
@@ -706,6 +712,31 @@ int small_bank_chunks(const Plan& p)
     int P = 1;
     while (P < 16 && longest >= 2 * P * 64) P *= 2;  // chunks of 64 samples or more
     return P;
+}
+
+// Largest lc ln|a1| over the filters, lc their bands' chunk lengths.
+double chunk_growth(const spiir_bank_desc* d, const Plan& p)
+{
+    double norm2[SPIIR_MAX_BANDS] = {}, most = -HUGE_VAL;  // largest |a1|^2 of a band
+    const double* a = d->a1;
+    for (int t = 0; t < p.T; ++t)
+        for (int h = 0; h < p.H; ++h)
+            for (int i = 0; i < d->n_filters[t * p.H + h]; ++i, a += 2)
+                norm2[h] = std::max(norm2[h], a[0] * a[0] + a[1] * a[1]);
+    for (int h = 0; h < p.H; ++h) most = std::max(most, 0.5 * p.lc[h] * std::log(norm2[h]));
+    return most;
+}
+
+// The chain pass multiplies start states by a1^lc in FP32.  Where that overflows
+// (filters with |a1| > 1) even a state of zero would turn NaN at the first chunk's
+// end, so such a bank runs whole.  ln of the largest FP32 value is 88.7.
+constexpr double kMaxGrowth = 88.0;
+
+// A bank whose descriptor or AUTO asks for p.P chunks.
+void set_chunks_run(const spiir_bank_desc* d, Plan& p)
+{
+    set_run(p, chunks_run(p));
+    if (p.P > 1 && chunk_growth(d, p) > kMaxGrowth) set_run(p, 1);
 }
 
 // The matrix-core engine's layout (single-rate banks): every template's
@@ -857,13 +888,12 @@ int make_plan(const spiir_bank_desc* d, Plan& p)
     if (d && d->engine == SPIIR_ENGINE_MFMA) return make_plan_mfma(d, p);
     if (!d || d->time_chunks != SPIIR_TIME_CHUNKS_AUTO) {
         const int rc = make_plan_fixed(d, p);
-        if (rc == SPIIR_OK && p.P > 1) set_chunks_run(p);
+        if (rc == SPIIR_OK && p.P > 1) set_chunks_run(d, p);
         else if (rc == SPIIR_OK && !d->filters_per_lane && !d->waves_per_group) {
             const int P = small_bank_chunks(p);
-            if (P > 1) {
-                set_chunks(p, P);
-                p.footprint += split_bytes(p);
-            }
+            if (P > 1) set_run(p, P);
+            // (a bank that did not ask for it is only split where every filter decays)
+            if (p.P > 1 && chunk_growth(d, p) >= 0.0) set_run(p, 1);
         }
         return rc;
     }
@@ -878,7 +908,7 @@ int make_plan(const spiir_bank_desc* d, Plan& p)
     d1.waves_per_group = p.W;
     d1.window_copies = p.copies;
     rc = make_plan_fixed(&d1, p);
-    if (rc == SPIIR_OK) set_chunks_run(p);
+    if (rc == SPIIR_OK) set_chunks_run(d, p);
     return rc;
 }
 

@@ -1,8 +1,11 @@
 """What the host library launches and keeps, on the CPU (tests/hoststub.py)."""
+import dataclasses
+
 import numpy as np
 import pytest
 
 import hoststub
+from paper_1702_02256_amd import spiir as S
 from paper_1702_02256_amd import workloads as W
 
 SHAPE = {"filters_per_lane": 4, "waves_per_group": 4}
@@ -37,3 +40,25 @@ def test_a_restored_state_clears_the_chunk_end_states(stub):
     bank.load_state(blob, stream=0)
     assert not ends.any() and not pending.any()
     bank.destroy()
+
+
+@pytest.mark.parametrize("F", [4, 2])
+@pytest.mark.parametrize("growth,lc,whole", [(0.9999, 256, False), (1.01, 512, False), (1.42, 256, True),
+                                             (1.0, 2048, False), (1.05, 2048, True), (1e200, 64, True)])
+def test_banks_whose_chain_overflows_run_whole(growth, lc, whole, F):
+    # a1^lc beyond FP32 would turn a state of zero into NaN: such banks are not cut
+    tb = _tables(2)
+    a1 = tb.a1.copy()
+    a1[7] = growth
+    tb = dataclasses.replace(tb, a1=a1)
+    shape = {"filters_per_lane": F, "waves_per_group": 4}
+    P = 4096 // lc if F == 2 or lc < 2048 else 1
+    asked = S.spiir_plan(tb, 4096, time_chunks=4096 // lc, **shape)
+    plain = S.spiir_plan(tb, 4096, **shape)
+    rows = 0 if whole or P == 1 else 2 + 2 * (P + 1) + 6
+    assert asked["footprint"] == plain["footprint"] + rows * 8 * asked["filter_slots"]
+    assert asked["time_chunks"] == 4096 // lc
+    # not asked for: only where every filter decays
+    own = S.spiir_plan(tb, 4096)
+    plain = S.spiir_plan(tb, 4096, **SHAPE)
+    assert (own["footprint"] > plain["footprint"]) == (growth < 1.0)
