@@ -267,7 +267,11 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
             if (wslot_src[i] >= 0) maxd = std::max(maxd, wslot_d[i]);
         w.maxd = maxd;
         // lane -> local piece (padding lanes join the last piece); runs end at a
-        // piece change or at the end of each 16-lane group
+        // piece change or at the end of each 16-lane group.  The 16-lane groups
+        // without a filter are no runs of any piece: a sample that is not finite
+        // makes their lanes NaN in k_filter, and the pipelined kernel leaves
+        // them out.
+        w.lanes = (cur.lanes + kRunLanes - 1) / kRunLanes * kRunLanes;
         std::vector<int> lp(L);
         for (int i = 0; i < L; ++i)
             lp[i] = (i < cur.lanes ? cur.lane_piece[i] : last_piece) - first_piece;
@@ -279,7 +283,7 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
             if (end) {
                 slot = run++;
                 if (run0[lp[i]] < 0) run0[lp[i]] = slot;
-                run1[lp[i]] = slot + 1;
+                if (i < w.lanes) run1[lp[i]] = slot + 1;
             }
             p.lane_meta.push_back((lp[i] << 16) | slot);
         }

@@ -61,7 +61,7 @@ struct WgDesc {
     int32_t meta_base;   // L lane-meta words: (piece << 16) | run slot (or kSlotNone)
     int32_t piece_base;  // first PieceDesc
     int32_t scale;       // matrix-core engine: log2 of the fp16 scale of its b0 a1^j
-    int32_t pad;
+    int32_t lanes;       // lanes of its 16-lane groups that hold filters (the first ones)
 };
 
 // A contiguous lane range of one (template, band) segment inside a workgroup.

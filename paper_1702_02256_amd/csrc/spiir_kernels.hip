@@ -685,6 +685,7 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
         }
     }
 
+    if (tid >= wg.lanes) return;  // the state of padding stays zero
     if (LOCAL) {
         SPIIR_AS_GLOBAL c32* ue = gmem(bd->uend) + (int64_t)tc * bd->n_slots;
 #pragma unroll
@@ -852,7 +853,6 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         pzoff[p] = piece_out(q, pd);
         prun[p] = make_int2(pd.run0, pd.run1);
     }
-    for (int i = tid; i < 2 * kTile * nrun; i += NT) l2buf[i] = c32{0.0f, 0.0f};
 
     float ar[NF], ai[NF], br[NF], bi[NF], dr[NF], di[NF], yr[NF], yi[NF], ur[NF], ui[NF];
     float er[NF], ei[NF], eur[NF], eui[NF];  // DUAL: the zero-start run of the chunk in progress
@@ -950,15 +950,9 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     float* const l2f = reinterpret_cast<float*>(l2buf);
     const int l2size = 2 * kTile * nrun;  // floats of one run-sum buffer
 
-    // A wave whose lanes hold no filter and no state (padding) adds exact
-    // zeros, as the run-sum buffers hold from the start: it takes no part in
-    // the tiles but their barriers and its level-2 tasks.
-    bool zero = true;
-#pragma unroll
-    for (int f = 0; f < NF; ++f)
-        zero &= ar[f] == 0.0f && ai[f] == 0.0f && br[f] == 0.0f && bi[f] == 0.0f && yr[f] == 0.0f && yi[f] == 0.0f &&
-                ur[f] == 0.0f && ui[f] == 0.0f;
-    const bool idle = __all(zero);
+    // A wave of padding lanes takes no part in the tiles but their barriers and
+    // its level-2 tasks (its run sums belong to no piece).
+    const bool idle = __builtin_amdgcn_readfirstlane(ln) >= wg.lanes;
 
     // the tiles in flight: first sample and length of the tile whose partial
     // sums are in pbuf (1) and of the one whose run sums are in l2buf (2)
@@ -1095,7 +1089,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
             const float ux = fmaf(dl_.x, st.x, fmaf(-dl_.y, st.y, er[f]));
             const float uy = fmaf(dl_.x, st.y, fmaf(dl_.y, st.x, ei[f]));
             st = c32{fmaf(al.x, st.x, fmaf(-al.y, st.y, ux)), fmaf(al.x, st.y, fmaf(al.y, st.x, uy))};
-            gmem(bd->s)[g] = unflip(st.x, st.y);
+            if (ln < wg.lanes) gmem(bd->s)[g] = unflip(st.x, st.y);
             er[f] = ei[f] = eur[f] = eui[f] = 0.0f;
             if (kend < nh) {
                 yr[f] = st.x;
@@ -1253,6 +1247,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         }
     }
 
+    if (ln >= wg.lanes) return;  // the state of padding stays zero
     if (LOCAL) {
         SPIIR_AS_GLOBAL c32* ue = gmem(bd->uend) + (int64_t)tc * bd->n_slots;
 #pragma unroll

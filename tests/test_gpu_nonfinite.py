@@ -1,4 +1,5 @@
-"""Non-finite samples: a restored state recovers the bank.
+"""Non-finite samples and states: the same results whichever filter kernel a
+launch takes, and a restored state that recovers the bank.
 
 A bank's workgroups end in lanes that hold no filter.  The pipelined kernel leaves
 whole waves of them out, k_filter launches them; which of the two runs depends on
@@ -66,6 +67,30 @@ def _stream(n, at, value):
     if at is not None:
         x[at] = value
     return torch.from_numpy(x).cuda()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("name", list(BANKS))
+def test_same_bits_whatever_shares_the_launch(fillers, name, value):
+    from paper_1702_02256_amd import spiir as S
+    tb = _tables(name)
+    x = _stream(3 * N, N + 100, value)
+    # a split bank's blocks of 128 samples run both recurrences in one workgroup
+    for kw, blocks in (({}, [N, N, N]), ({"time_chunks": 4}, [N, N, N]), ({"time_chunks": 4}, [128] * 12)):
+        bank = S.Bank(tb, N, **SHAPE, **kw)
+        ref = None
+        for n_wg in FILL:
+            print(f"{name}, {value}, {kw}: {n_wg} workgroups beside it", flush=True)
+            bank.reset()
+            z = _run(bank, x, blocks, fillers.get(n_wg))
+            state = np.frombuffer(bank.save_state(), np.uint8)[128:]
+            rc, flags = bank.status()
+            assert rc == S.SPIIR_ENONFINITE and flags.all()
+            got = (_bits(z), _bits(state), flags)
+            ref = ref or got
+            for a, b in zip(got, ref):
+                assert np.array_equal(a, b), (name, kw, n_wg)
+        bank.destroy()
 
 
 @pytest.mark.parametrize("kw", [{}, {"time_chunks": 4}])
