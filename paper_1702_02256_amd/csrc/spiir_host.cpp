@@ -1253,9 +1253,26 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                         : ra.nchunk > 1                                              ? kDirectSplit
                                                                                     : kDirect;
             ra.nblocks = p.n_groups;
-            ra.z_direct = ra.direct && ra.z && !ra.peaks;
-            ra.T = ra.z_direct && p.whole_templates ? 0 : p.T;
             need_stage |= !ra.direct;
+        }
+        // z written where the filter launch still reads some request's x (a block
+        // filtered in place) would race: such requests keep the pass that writes z
+        // after every x was read
+        auto overwrites_input = [&](int k) {
+            const ReqArg& w = A.req[k];
+            const uintptr_t z0 = (uintptr_t)w.z;
+            const uintptr_t z1 = (uintptr_t)(w.z + (req[rmap[k]].bank->plan.T - 1) * w.ldz + w.n);
+            for (int i = 0; i < A.nreq; ++i) {
+                const ReqArg& r = A.req[i];
+                if (r.direct == kDirect && (uintptr_t)r.x < z1 && z0 < (uintptr_t)(r.x + r.n)) return true;
+            }
+            return false;
+        };
+        for (int k = 0; k < A.nreq; ++k) {
+            const Plan& p = req[rmap[k]].bank->plan;
+            ReqArg& ra = A.req[k];
+            ra.z_direct = ra.direct && ra.z && !ra.peaks && !overwrites_input(k);
+            ra.T = ra.z_direct && p.whole_templates ? 0 : p.T;
         }
         // filter workgroups of one shape: band-major across requests (longest
         // bands first), chunk-major inside a (band, request) segment when split

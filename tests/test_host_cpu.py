@@ -62,3 +62,37 @@ def test_banks_whose_chain_overflows_run_whole(growth, lc, whole, F):
     own = S.spiir_plan(tb, 4096)
     plain = S.spiir_plan(tb, 4096, **SHAPE)
     assert (own["footprint"] > plain["footprint"]) == (growth < 1.0)
+
+
+def test_a_block_filtered_in_place_keeps_the_pass_that_writes_z(stub):
+    # the filter launch reads x in every workgroup, so it must not write z over it
+    n = 1000
+    bank = stub.bank(_tables(3), n, **SHAPE)
+    other = stub.bank(_tables(2, seed=4), n, **SHAPE)
+    staged = stub.bank(_tables(2, H=2, seed=5), n, **SHAPE)
+    buf = np.zeros(40 * n, np.float32)  # z of `bank`: floats [2n, 8n)
+    z = buf[2 * n:8 * n].view(np.complex64).reshape(3, n)
+
+    def direct(requests):
+        filters = [l for l in stub.process(requests) if l.kind in ("filter", "pipe")]
+        last = [r for l in stub.launches() if l.kind == "upadd" for r in l.req]
+        got = [r.z_direct for r in filters[0].req]
+        assert [r.T for r in filters[0].req] == [0 if d else b.n_templates for d, (b, _, _) in zip(got, requests)]
+        assert bool(last) == (0 in got)
+        return got
+
+    for at, apart in ((0, 1), (n, 1), (n + 1, 0), (2 * n, 0), (5 * n, 0), (8 * n - 1, 0), (8 * n, 1)):
+        assert direct([(bank, buf[at:at + n], z)]) == [apart], at
+    # another request's x in the same launch; a staged request has read its own before
+    free = buf[10 * n:].view(np.complex64)
+    zo = free[:2 * n].reshape(2, n)
+    assert direct([(bank, buf[:n], z), (other, buf[3 * n:4 * n], zo)]) == [0, 1]
+    assert direct([(bank, buf[:n], z), (other, buf[9 * n:10 * n], zo)]) == [1, 1]
+    # rows with a stride: the gaps count as z
+    wide = free[:9 * n].reshape(3, 3 * n)[:, :n]
+    assert direct([(bank, buf[10 * n + 4 * n:10 * n + 5 * n], wide)]) == [0]
+    launches = stub.process([(bank, buf[:n], z), (staged, buf[3 * n:4 * n], zo)])
+    assert [l.kind for l in launches][0] == "stage"
+    assert [r.z_direct for r in [l for l in launches if l.kind in ("filter", "pipe")][0].req] == [1, 0]
+    for b in (bank, other, staged):
+        b.destroy()
