@@ -401,9 +401,9 @@ def _torch_hip_first():
 
 
 def _blob_bytes(blob: bytes) -> int:
-    """Length of a state blob by its header (0 if it has none)."""
+    """Length of a state blob by its header (-1 if it has none)."""
     if len(blob) < 128:
-        return 0
+        return -1
     version, T = struct.unpack_from("<Ii", blob, 4)
     slots, ring, _, hist = struct.unpack_from("<4q", blob, 32)
     return 128 + slots * (16 if version == 3 else 40) + 4 * ring + 8 * hist + 4 * T

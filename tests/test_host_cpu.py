@@ -96,3 +96,16 @@ def test_a_block_filtered_in_place_keeps_the_pass_that_writes_z(stub):
     assert [r.z_direct for r in [l for l in launches if l.kind in ("filter", "pipe")][0].req] == [1, 0]
     for b in (bank, other, staged):
         b.destroy()
+
+
+@pytest.mark.parametrize("n", [0, 1, 127, 128])
+def test_a_blob_without_a_header_is_refused(stub, monkeypatch, n):
+    # the library reads the header before it knows the length
+    bank = stub.bank(_tables(1), 512, **SHAPE)
+    called = []
+    real = stub.lib.spiir_load_state
+    monkeypatch.setattr(stub.lib, "spiir_load_state", lambda h, buf, s: called.append(len(buf)) or real(h, buf, s))
+    with pytest.raises(S.SpiirError):
+        bank.load_state(bytes(n), stream=0)
+    assert called == ([128] if n == 128 else [])
+    bank.destroy()
