@@ -1348,8 +1348,10 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             return local ? launch_filter_local(sh.F, sh.prec, X, nblocks, sh.L, lds, s)
                          : launch_filter(sh.F, sh.prec, X, nblocks, sh.L, lds, s);
         };
-        mark(0);
-        if (need_stage) e = (hipError_t)launch_stage(A, lds_s, s);
+        if (need_stage) {
+            mark(0);
+            e = (hipError_t)launch_stage(A, lds_s, s);
+        }
         mark(1);
         if (split)
             for (const Shape* sp = shape_buf; sp != shapes_end; ++sp) {
@@ -1368,11 +1370,13 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                 e = (hipError_t)run_filter(sh, X, n0, false);
         }
         mark(2);
-        if (e == hipSuccess && ntm > 0) e = (hipError_t)launch_upadd(A, ntm, lds_u, s);
-        mark(3);
+        if (e == hipSuccess && ntm > 0) {
+            e = (hipError_t)launch_upadd(A, ntm, lds_u, s);
+            mark(3);
+        }
         if (prof)
             for (int i = 0; i < 3; ++i)
-                if (ev[i] && ev[i + 1] && (i != 0 || need_stage) && (i != 2 || ntm > 0)) g_prof_recs.push_back(ProfRec{i, ev[i], ev[i + 1]});
+                if (ev[i] && ev[i + 1]) g_prof_recs.push_back(ProfRec{i, ev[i], ev[i + 1]});
     }
     return e;
 }

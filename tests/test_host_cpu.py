@@ -1,4 +1,5 @@
 """What the host library launches and keeps, on the CPU (tests/hoststub.py)."""
+import ctypes as C
 import dataclasses
 
 import numpy as np
@@ -108,4 +109,23 @@ def test_a_blob_without_a_header_is_refused(stub, monkeypatch, n):
     with pytest.raises(S.SpiirError):
         bank.load_state(bytes(n), stream=0)
     assert called == ([128] if n == 128 else [])
+    bank.destroy()
+
+
+@pytest.mark.parametrize("H", [1, 2])
+def test_profiled_calls_reuse_their_events(stub, H):
+    # every event taken for a call comes back, also where a kind of kernel is not launched
+    bank = stub.bank(_tables(2, H), 4096, **SHAPE)
+    x, z = _io(bank, 4096)
+    lib, counts = stub.lib, []
+    for _ in range(4):
+        assert lib.spiir_profile_enable(1) == S.SPIIR_OK
+        for _ in range(5):
+            stub.process([(bank, x, z)])
+        data = S.ProfileData()
+        assert lib.spiir_profile_read(C.byref(data)) == S.SPIIR_OK
+        assert list(data.launches) == ([0, 5, 0] if H == 1 else [5, 5, 5])
+        counts.append(stub.events())
+    lib.spiir_profile_enable(0)
+    assert len(set(counts)) == 1, counts
     bank.destroy()
