@@ -423,20 +423,52 @@ __device__ __forceinline__ Chunk chunk_range(int c, int nchunk, int64_t s0h, int
 // chunk starts on a carry-chunk boundary, so u = dC * y there.  The end-state
 // pass copies the carried state (y0, ys0) for the filter pass, whose last chunk
 // overwrites it.
+//
+// Which arrays a workgroup reads is decided once, and per slot the values are
+// selected, without branches around arithmetic: with the product dC * y in a
+// branch of its own, the compiler moved the negation of dC, which the sample
+// loop uses too, into some of the branches and left the register undefined on
+// another path.
+struct Start {
+    const c32 *y, *u;
+    bool fresh;  // a chunk starts here: u = dC * y
+};
+
 template <bool LOCAL>
-__device__ __forceinline__ void start_state(CBankDev* bd, int nchunk, int tc, int64_t g, const c32& d, c32& y, c32& u)
+__device__ __forceinline__ Start start_from(CBankDev* bd, int nchunk, int tc)
 {
-    if (nchunk > 1 && tc > 0) {
-        y = LOCAL ? c32{0.0f, 0.0f} : gmem(bd->schain)[(int64_t)tc * bd->n_slots + g];
-        u = c32{fmaf(d.x, y.x, -d.y * y.y), fmaf(d.x, y.y, d.y * y.x)};
-    } else if (LOCAL) {
-        gmem(bd->y0)[g] = gmem(bd->y)[g];
-        gmem(bd->ys0)[g] = gmem(bd->ys)[g];
-        y = gmem(bd->ey)[g];
-        u = gmem(bd->eu)[g];
+    Start st;
+    st.fresh = nchunk > 1 && tc > 0;
+    if (LOCAL) {
+        st.y = bd->ey;
+        st.u = bd->eu;
     } else {
-        y = gmem(nchunk > 1 ? bd->y0 : bd->y)[g];
-        u = gmem(nchunk > 1 ? bd->ys0 : bd->ys)[g];
+        st.y = st.fresh ? bd->schain + (int64_t)tc * bd->n_slots : nchunk > 1 ? bd->y0 : bd->y;
+        st.u = nchunk > 1 ? bd->ys0 : bd->ys;
+    }
+    if (st.fresh) st.u = st.y;  // not used: the same words again
+    return st;
+}
+
+// The carried state, kept for the filter pass.
+__device__ __forceinline__ void save_state(CBankDev* bd, int64_t g)
+{
+    const c32 y = gmem(bd->y)[g], u = gmem(bd->ys)[g];
+    gmem(bd->y0)[g] = y;
+    gmem(bd->ys0)[g] = u;
+}
+
+template <bool LOCAL>
+__device__ __forceinline__ void start_state(const Start& st, int64_t g, const c32& d, c32& y, c32& u)
+{
+    y = gmem(st.y)[g];
+    u = gmem(st.u)[g];
+    const c32 v{fmaf(d.x, y.x, -d.y * y.y), fmaf(d.x, y.y, d.y * y.x)};
+    u.x = st.fresh ? (LOCAL ? 0.0f : v.x) : u.x;
+    u.y = st.fresh ? (LOCAL ? 0.0f : v.y) : u.y;
+    if (LOCAL) {
+        y.x = st.fresh ? 0.0f : y.x;
+        y.y = st.fresh ? 0.0f : y.y;
     }
 }
 
@@ -497,12 +529,13 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 
     float ar[F], ai[F], br[F], bi[F], dr[F], di[F], yr[F], yi[F], ur[F], ui[F];
     int dl[F];
+    const Start st = start_from<LOCAL>(bd, q.nchunk, tc);
 #pragma unroll
     for (int f = 0; f < F; ++f) {
         const int64_t g = wg.slot_base + (int64_t)f * L + tid;
         const c32 a = cmem(bd->a)[g], b = cmem(bd->b)[g], d = cmem(bd->dc)[g];
         c32 y, u;
-        start_state<LOCAL>(bd, q.nchunk, tc, g, d, y, u);
+        start_state<LOCAL>(st, g, d, y, u);
         ar[f] = a.x; ai[f] = a.y;
         br[f] = b.x; bi[f] = b.y;
         dr[f] = d.x; di[f] = d.y;
@@ -510,6 +543,9 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
         ur[f] = u.x; ui[f] = u.y;
         dl[f] = cmem(bd->off)[g];
     }
+    if (LOCAL && !st.fresh)
+#pragma unroll
+        for (int f = 0; f < F; ++f) save_state(bd, wg.slot_base + (int64_t)f * L + tid);
     // without it a lone workgroup of 512 lanes waits in its tile loop: 15 templates, 7
     // bands, 3 streams of up to 14720 samples 2934 us, with it 2742
     wait_loads();
@@ -738,8 +774,11 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 // 512 multi-rate templates, 4096 samples 534 -> 375 (X = 2); 1024 of them
 // 575 -> 427 (X = 1); 160 of them, 576 samples 88 -> 61 (X = 2).
 //
-// At most kPipeThreads threads, so that a lane may hold 256 registers: a spilled
-// register would be read back behind the workspace stores, a microsecond.
+// At most kPipeThreads threads, so that a lane may hold 256 registers: a register
+// spilled in the tile loop would be read back behind the workspace stores, a
+// microsecond.  X = 2 uses up to 186 of them (245 with the zero-start run), X = 4 134
+// (173), X = 1 all and spills 25 (32 with the compensated sum), which are read back
+// once per window, outside the tile loop.
 // ---------------------------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v)
@@ -794,15 +833,17 @@ __device__ __forceinline__ void wait_lds() { __builtin_amdgcn_s_waitcnt(0xC07F);
 // tile_full), while arithmetic may still move across.
 __device__ __forceinline__ void keep_single() { __builtin_amdgcn_sched_barrier(0x6); }
 
-constexpr int kAhead = 4;     // x pairs read ahead
-constexpr int kRunAhead = 8;  // run sums a level-2 task reads ahead
-
+constexpr int kAhead = 4;  // x pairs read ahead
 
 template <int F, int X, bool COMP, bool LOCAL, bool DUAL>
 __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
 {
     constexpr int NF = F / X;
     constexpr int kPairs = kRunLanes / 2;
+    // run sums a level-2 task reads ahead: with one thread per lane eight of them
+    // add spills (1024 multi-rate templates, 4096 and 512 samples 437 and 92 us, six
+    // 429 and 87; the compensated sum 466, 446)
+    constexpr int kRunAhead = X == 1 ? 6 : 8;
     using Acc = typename std::conditional<COMP, double, float>::type;
     extern __shared__ float sm[];
     const int bid = blockIdx.x;
@@ -861,19 +902,26 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
     const int lc = bd->lc[h];
     const int to_boundary = dual ? lc - (int)(s0h % lc) : 0;  // samples to the end of the chunk in progress
     const int64_t slot0_ = wg.slot_base + (int64_t)part * NF * L + ln;
+    Start st = start_from<LOCAL>(bd, q.nchunk, tc);
+    if (dual && to_boundary == lc) {  // the block starts a chunk
+        st.y = st.u = bd->s;
+        st.fresh = true;
+    }
+    const c32* ey = dual ? bd->ey : st.y;
+    const c32* eys = dual ? bd->eu : st.u;
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
         const int64_t g = slot0_ + (int64_t)f * L;
         c32 a = cmem(bd->a)[g], b = cmem(bd->b)[g], d = cmem(bd->dc)[g], y, u;
-        start_state<LOCAL>(bd, q.nchunk, tc, g, d, y, u);
+        start_state<LOCAL>(st, g, d, y, u);
         c32 e{0.0f, 0.0f}, eu{0.0f, 0.0f};
-        if (dual) {
-            if (to_boundary == lc) {  // the block starts a chunk
-                y = gmem(bd->s)[g];
-                u = c32{fmaf(d.x, y.x, -d.y * y.y), fmaf(d.x, y.y, d.y * y.x)};
-            }
-            e = gmem(bd->ey)[g];
-            eu = gmem(bd->eu)[g];
+        if (DUAL) {
+            e = gmem(ey)[g];
+            eu = gmem(eys)[g];
+            e.x = dual ? e.x : 0.0f;
+            e.y = dual ? e.y : 0.0f;
+            eu.x = dual ? eu.x : 0.0f;
+            eu.y = dual ? eu.y : 0.0f;
         }
         if (flip) {
             e = c32{e.y, e.x};
@@ -893,6 +941,9 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         eur[f] = eu.x; eui[f] = eu.y;
         dl[f] = cmem(bd->off)[g];
     }
+    if (LOCAL && !st.fresh)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) save_state(bd, slot0_ + (int64_t)f * L);
     __syncthreads();
 
     // Level-1 role: sample row j1 of the 16-lane group q1 (the wave's own
