@@ -33,7 +33,7 @@ constexpr int kNoFit = 1;           // internal: this launch shape exceeds the L
 constexpr int kXcapMax = 24576;     // LDS window, floats
 constexpr int kMaxLds = 160 * 1024;
 constexpr int kComputeUnits = 256;  // MI355X
-constexpr int kDualSamples = 256;   // shortest block of a bank split in time that runs in chunks
+constexpr int kDualSamples = 256;   // blocks of a bank split in time that run in one launch
 constexpr uint32_t kStateMagic = 0x53504952u;  // "SPIR"
 constexpr uint32_t kStateVersion = 3;  // 3: 128-byte header with the layout fingerprint
 constexpr uint32_t kStateVersionSplit = 4;  // 4: and at the end the carried state of a time split
@@ -1118,13 +1118,12 @@ hipError_t wait_banks(int32_t n_req, const spiir_request* req, hipStream_t s)
 const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 
 // Threads per lane of the pipelined filter kernel for a launch, or 0 for
-// k_filter, which the results do not depend on.  `rounds`: the launch's work in
-// workgroups as long as its longest (its samples over the longest
-// workgroup's), `lanes` the most lanes of a workgroup that hold filters.  The
+// k_filter, which the results do not depend on.  `g`: the launch's work in
+// groups of 256 lanes as long as its longest workgroup, per compute unit; `lanes` the
+// most lanes of a workgroup that hold filters.  The
 // pipelined kernel wins while the compute units are short of waves, k_filter
 // (four waves per SIMD, half the registers) once they are not.  Measured, us
-// per block, k_filter / X = 2 / X = 1 by groups of 256 lanes per compute unit
-// (g): multi-rate banks of 64, 700, 1024, 1400, 2048 templates (g = 0.08, 0.91,
+// per block, k_filter / X = 2 / X = 1 by g: multi-rate banks of 64, 700, 1024, 1400, 2048 templates (g = 0.08, 0.91,
 // 1.33, 1.82, 2.63) 526 / 333 / 393, 548 / 374 / 422, 589 / 530 / 438,
 // 633 / 702 / 545, 711 / 972 / 753; single-rate banks of 64, 512, 768
 // templates of 512 filters (g = 0.12, 1, 1.5) 268 / 159 / 188, 284 / 179 / 207,
@@ -1141,9 +1140,8 @@ const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 // X = 2: 833 workgroups (700 templates, 7 bands) 53 / 64, 61 / 68, 93 / 90; 609 (512
 // templates) 51 / 53, 59 / 58, 91 / 74; 364 (1024 templates, 3 bands) 48 / 43, 57 / 48,
 // 93 / 72; 208 (700 single-rate templates) 41 / 36, 49 / 41, 82 / 63.
-int pipe_threads(int F, int lanes, int longest, double rounds, int64_t groups)
+int pipe_threads(int F, int lanes, int longest, double g, int64_t groups)
 {
-    const double g = rounds * lanes / (256.0 * kComputeUnits);
     if (F != 4 || 2 * lanes > kPipeThreads || g > 2.0) return 0;
     const int x = g > 1.0 ? 1 : 4 * lanes <= kPipeThreads ? 4 : 2;
     const bool many = groups > 2 * kComputeUnits;
@@ -1184,7 +1182,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             ra.H = p.H;
             ra.c0 = (int32_t)c0;
             ra.thr2 = thr2;
-            // (dual: see below)
+            // (dual: see one_launch below)
             ra.dual = p.P > 1 && p.F == 4 && ra.n <= std::max(2 * p.lc[0], kDualSamples);
             ra.nchunk = p.P > 1 && !ra.dual ? p.P + 1 : 1;
             lds_s = std::max(lds_s, p.lds_stage);
@@ -1212,7 +1210,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         }
         const Shape* const shapes_end = shape_buf + nshape;
         // how full a shape's launch over the requests of X makes the device (pipe_threads)
-        auto threads_of = [&](const Shape& sh, const LaunchArgs& X, int* lanes_out) {
+        auto threads_of = [&](const Shape& sh, const LaunchArgs& X, int* lanes_out, double* fill = nullptr) {
             int64_t work = 0, groups = 0;  // samples of all workgroups, and of the longest
             int longest = 1, lanes = 64;
             bool dual = false;
@@ -1229,21 +1227,39 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
                     longest = std::max(longest, X.req[k].nchunk > 1 ? std::min(nh, p.lc[h]) : nh);
                 }
             }
+            const double g = (double)work / longest * lanes / (256.0 * kComputeUnits);
             if (lanes_out) *lanes_out = lanes;
-            return pipe_threads(sh.F, lanes, dual ? std::max(longest, 8 * kTile) : longest, (double)work / longest,
-                                dual ? 0 : groups);
+            if (fill) *fill = g;
+            return pipe_threads(sh.F, lanes, dual ? std::max(longest, 8 * kTile) : longest, g, dual ? 0 : groups);
         };
-        // A short block of a bank split in time (two chunks) runs in one launch,
-        // its chunks in turn in one workgroup that carries both runs, where
-        // the pipelined kernel has the registers (X > 1).  One template, 7
-        // bands: 64 samples 42 (in chunks) / 28 us, 256 samples 44 / 35.
+        // A short block of a bank split in time runs in one launch, its chunks in
+        // turn in one workgroup that carries both runs, where the pipelined kernel
+        // has the registers (X > 1); the results are those of the three launches.
+        // These cost more at the start and less per sample.  Measured, us, one
+        // launch / three, blocks of 256, 384, 512 samples, chunks of 256:
+        //   X = 4: one template in 7 bands 34 / 44, 38 / 47, 43 / 46 (chunks of 512,
+        //     blocks of 768, 1024: 54 / 59, 66 / 59)
+        //   X = 2: 4 templates in 7 bands 42 / 51, 51 / 53, 61 / 55; 45 in 5 bands 55 /
+        //     57, 71 / 61, 86 / 64, 4 such banks (g = 0.24) 71 / 82, 86 / 83, 102 / 84
+        //   16 banks of 12 (0.36) and 45 (0.97) such templates 128 / 143, 143 / 151,
+        //     160 / 158 and 146 / 197, 161 / 174, 177 / 182
+        //   chunks of 512, blocks of 512, 1024: 160 templates in 7 bands (0.21) 90 / 99,
+        //     152 / 100, 512 (0.67) 94 / 121, 157 / 139
+        auto one_launch = [&](int k, int x, double g) {
+            if (x < 2) return false;
+            const int n = x == 4 ? 3 * kDualSamples : g > 0.3 ? 2 * kDualSamples : kDualSamples;
+            return A.req[k].n <= std::max(req[rmap[k]].bank->plan.lc[0], n);
+        };
         for (const Shape* sp = shape_buf; sp != shapes_end; ++sp)
-            if (threads_of(*sp, A, nullptr) < 2)
+            for (int pass = 0; pass < 2; ++pass) {  // (the second: without those of the first)
+                double g = 0.0;
+                const int x = threads_of(*sp, A, nullptr, &g);
                 for (int k = 0; k < A.nreq; ++k)
-                    if (same(shape_of(k), *sp) && A.req[k].dual) {
+                    if (same(shape_of(k), *sp) && A.req[k].dual && !(pass ? x >= 2 : one_launch(k, x, g))) {
                         A.req[k].dual = 0;
                         A.req[k].nchunk = req[rmap[k]].bank->plan.P + 1;
                     }
+            }
         for (int k = 0; k < A.nreq; ++k) {
             const Plan& p = req[rmap[k]].bank->plan;
             ReqArg& ra = A.req[k];

@@ -129,3 +129,25 @@ def test_profiled_calls_reuse_their_events(stub, H):
     lib.spiir_profile_enable(0)
     assert len(set(counts)) == 1, counts
     bank.destroy()
+
+
+def test_short_blocks_of_split_banks_take_the_cheaper_route(stub):
+    # (templates, banks in the batch, n) -> one launch of both runs, or three launches
+    routes = [(1, 1, 256, 1), (1, 1, 512, 1), (40, 1, 256, 1), (40, 1, 320, 0), (40, 1, 512, 0), (40, 4, 512, 0),
+              (20, 16, 512, 1), (4, 1, 512, 0), (40, 16, 512, 1), (40, 16, 528, 0), (1, 1, 4096, 0)]
+    nf = np.random.default_rng(1).integers(40, 301, size=(40, 5)).astype(np.int32)
+    full = W.random_bank(6, nf, 4096, [2047 >> h for h in range(5)])
+    for T, nb, n, one in routes:
+        tb = full.subset(list(range(T))) if T < 40 else full
+        banks = [stub.bank(tb, 4096) for _ in range(nb)]
+        launches = stub.process([(b, *_io(b, n)) for b in banks])
+        kinds = [l.kind for l in launches]
+        assert ("chain" in kinds) == (not one), (T, nb, n, kinds)
+        assert all(r.dual == one for l in launches if l.kind == "pipe" for r in l.req), (T, nb, n)
+        for b in banks:
+            b.destroy()
+    # chunks of 512 samples that were asked for
+    bank = stub.bank(full, 4096, time_chunks=8)
+    for n, one in ((512, 1), (528, 0), (1024, 0)):
+        assert ("chain" in [l.kind for l in stub.process([(bank, *_io(bank, n))])]) == (not one), n
+    bank.destroy()
