@@ -997,9 +997,9 @@ hipError_t dalloc(T** p, size_t count)
 void free_bank(spiir_bank* b)
 {
     if (!b) return;
-    void* ptrs[] = {b->a,     b->b,     b->dc, b->y,  b->ys, b->off, b->wg,     b->piece, b->seg,
-                    b->lane_meta, b->rings, b->hd, b->hu, b->zw, b->uphist, b->flags, b->clock, b->al, b->uend, b->schain,
-                    b->s,  // with ey, eu, euend, y0, ys0
+    void* ptrs[] = {b->a,     b->b,     b->dc, b->y,  b->off, b->wg,     b->piece, b->seg,  // (ys lies behind y)
+                    b->lane_meta, b->rings, b->hd, b->hu, b->zw, b->uphist, b->flags, b->clock,
+                    b->s,  // the time split's arrays, see alloc_bank
                     b->kc, b->pw, b->bd};
     for (void* q : ptrs)
         if (q) (void)hipFree(q);
@@ -1007,23 +1007,15 @@ void free_bank(spiir_bank* b)
     delete b;
 }
 
-// Zero chunk end states: lanes of padding that a launch leaves out never write
-// theirs, and k_chain reads every slot's.
-int clear_end_states(spiir_bank* b, hipStream_t s)
-{
-    const Plan& p = b->plan;
-    if (p.P <= 1) return 0;
-    return launch_fill(b->euend, p.n_slots * (int64_t)sizeof(c32), s) |
-           launch_fill(b->uend, (p.P + 1) * p.n_slots * (int64_t)sizeof(c32), s);
-}
+// Rows of n_slots values from euend on that hold chunk end states (euend, uend).
+int64_t end_rows(const Plan& p) { return 1 + (p.P + 1); }
 
 int zero_state(spiir_bank* b, hipStream_t s)
 {
     const Plan& p = b->plan;
-    int e = clear_end_states(b, s);
-    e |= launch_fill(b->y, p.n_slots * (int64_t)sizeof(c32), s);
-    e |= launch_fill(b->ys, p.n_slots * (int64_t)sizeof(c32), s);
-    if (p.P > 1) e |= launch_fill(b->s, 3 * p.n_slots * (int64_t)sizeof(c32), s);  // s, ey, eu
+    int e = 0;
+    e |= launch_fill(b->y, 2 * p.n_slots * (int64_t)sizeof(c32), s);  // y, ys
+    if (p.P > 1) e |= launch_fill(b->s, (3 + end_rows(p)) * p.n_slots * (int64_t)sizeof(c32), s);  // s, ey, eu, end states
     e |= launch_fill(b->rings, p.ring_total * (int64_t)sizeof(float), s);
     e |= launch_fill(b->uphist, (int64_t)p.T * p.H * p.hu_len * (int64_t)sizeof(c32), s);
     e |= launch_fill(b->flags, (int64_t)p.T * (int64_t)sizeof(int32_t), s);
@@ -1504,8 +1496,8 @@ static bool alloc_bank(spiir_bank* b)
     ok &= dalloc(&b->a, p.n_slots) == hipSuccess;
     ok &= dalloc(&b->b, p.n_slots) == hipSuccess;
     ok &= dalloc(&b->dc, p.n_slots) == hipSuccess;
-    ok &= dalloc(&b->y, p.n_slots) == hipSuccess;
-    ok &= dalloc(&b->ys, p.n_slots) == hipSuccess;
+    ok &= dalloc(&b->y, 2 * (size_t)p.n_slots) == hipSuccess;
+    if (b->y) b->ys = b->y + p.n_slots;
     ok &= dalloc(&b->off, p.n_slots) == hipSuccess;
     ok &= dalloc(&b->wg, p.n_groups) == hipSuccess;
     ok &= dalloc(&b->piece, p.n_pieces) == hipSuccess;
@@ -1519,14 +1511,20 @@ static bool alloc_bank(spiir_bank* b)
     ok &= dalloc(&b->flags, p.T) == hipSuccess;
     ok &= dalloc(&b->clock, 3) == hipSuccess;
     if (p.P > 1) {
-        ok &= dalloc(&b->al, 2 * (size_t)p.n_slots) == hipSuccess;
-        ok &= dalloc(&b->uend, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
-        ok &= dalloc(&b->schain, (size_t)(p.P + 1) * p.n_slots) == hipSuccess;
-        // one allocation: s, ey, eu, euend, then y0, ys0
-        ok &= dalloc(&b->s, 6 * (size_t)p.n_slots) == hipSuccess;
+        // one allocation, what a reset zeroes first and in one piece
+        ok &= dalloc(&b->s, split_bytes(p) / sizeof(c32)) == hipSuccess;
         if (b->s) {
             c32* next = b->s;
-            for (c32** a : {&b->ey, &b->eu, &b->euend, &b->y0, &b->ys0}) *a = next += p.n_slots;
+            auto rows = [&](c32** a, int n) {
+                *a = next;
+                next += n * p.n_slots;
+            };
+            for (c32** a : {&b->s, &b->ey, &b->eu, &b->euend}) rows(a, 1);
+            rows(&b->uend, p.P + 1);
+            rows(&b->schain, p.P + 1);
+            rows(&b->al, 2);
+            rows(&b->y0, 1);
+            rows(&b->ys0, 1);
         }
     }
     if (p.engine == SPIIR_ENGINE_MFMA) {
@@ -1648,26 +1646,29 @@ int spiir_create(const spiir_bank_desc* desc, void* stream, spiir_bank** out)
         return SPIIR_ENOMEM;
     }
 
-    // tables in lane order; coefficients go through the FP64 prep kernel
-    c64* da = nullptr;
-    c64* db = nullptr;
-    std::vector<c64> ha, hb;
+    // tables in lane order, staged in one piece; coefficients go through the FP64
+    // prep kernel: a1, b0 and, for a time split, the exponent of a1^lc (the chunk
+    // length of the slot's band)
+    const int64_t ns = p.n_slots;
+    std::vector<c64> staged;
     try {
-        ha.resize((size_t)p.n_slots);
-        hb.resize((size_t)p.n_slots);
+        staged.assign((size_t)(2 * ns + (p.P > 1 ? (ns + 3) / 4 : 0)), c64{0.0, 0.0});
     } catch (const std::bad_alloc&) {
         free_bank(b);
         return SPIIR_ENOMEM;
     }
-    for (int64_t g = 0; g < p.n_slots; ++g) {
+    c64* const ha = staged.data();
+    c64* const hb = ha + ns;
+    for (int64_t g = 0; g < ns; ++g) {
         const int64_t src = p.slot_src[g];
-        if (src >= 0) {
-            ha[g] = c64{desc->a1[2 * src], desc->a1[2 * src + 1]};
-            hb[g] = c64{desc->b0[2 * src], desc->b0[2 * src + 1]};
-        } else {
-            ha[g] = c64{0.0, 0.0};
-            hb[g] = c64{0.0, 0.0};
-        }
+        if (src < 0) continue;
+        ha[g] = c64{desc->a1[2 * src], desc->a1[2 * src + 1]};
+        hb[g] = c64{desc->b0[2 * src], desc->b0[2 * src + 1]};
+    }
+    if (p.P > 1) {
+        int32_t* hlc = reinterpret_cast<int32_t*>(hb + ns);
+        const int64_t per_wg = (int64_t)p.F * p.L;
+        for (int64_t g = 0; g < ns; ++g) hlc[g] = p.lc[p.wg[g / per_wg].band];
     }
     std::vector<float> hd(p.td, 1.0f), hu(p.tu, 1.0f);
     if (p.H > 1) {
@@ -1680,33 +1681,14 @@ int spiir_create(const spiir_bank_desc* desc, void* stream, spiir_bank** out)
     auto up = [&](void* dst, const void* src, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, src, bytes, hipMemcpyHostToDevice, s);
     };
-    if (hipMalloc((void**)&da, sizeof(c64) * std::max<int64_t>(p.n_slots, 1)) != hipSuccess ||
-        hipMalloc((void**)&db, sizeof(c64) * std::max<int64_t>(p.n_slots, 1)) != hipSuccess) {
-        if (da) (void)hipFree(da);
-        if (db) (void)hipFree(db);
+    c64* da = nullptr;
+    if (dalloc(&da, staged.size()) != hipSuccess) {
         (void)hipGetLastError();
         free_bank(b);
         return SPIIR_ENOMEM;
     }
-    // time split: per-slot exponent of a1^lc (the slot's band chunk length)
-    int32_t* dlc = nullptr;
-    std::vector<int32_t> hlc;
-    if (p.P > 1) {
-        hlc.resize((size_t)p.n_slots);
-        const int64_t per_wg = (int64_t)p.F * p.L;
-        for (size_t w = 0; w < p.wg.size(); ++w)
-            for (int64_t i = 0; i < per_wg; ++i) hlc[w * per_wg + i] = p.lc[p.wg[w].band];
-        if (hipMalloc((void**)&dlc, sizeof(int32_t) * std::max<int64_t>(p.n_slots, 1)) != hipSuccess) {
-            (void)hipFree(da);
-            (void)hipFree(db);
-            (void)hipGetLastError();
-            free_bank(b);
-            return SPIIR_ENOMEM;
-        }
-        up(dlc, hlc.data(), sizeof(int32_t) * p.n_slots);
-    }
-    up(da, ha.data(), sizeof(c64) * p.n_slots);
-    up(db, hb.data(), sizeof(c64) * p.n_slots);
+    const int32_t* dlc = p.P > 1 ? reinterpret_cast<const int32_t*>(da + 2 * ns) : nullptr;
+    up(da, ha, sizeof(c64) * staged.size());
     up(b->off, p.slot_off.data(), sizeof(int32_t) * p.n_slots);
     up(b->wg, p.wg.data(), sizeof(WgDesc) * p.wg.size());
     up(b->piece, p.piece.data(), sizeof(PieceDesc) * p.piece.size());
@@ -1754,13 +1736,11 @@ int spiir_create(const spiir_bank_desc* desc, void* stream, spiir_bank** out)
         up(b->kc, mkc.data(), sizeof(c32) * p.n_slots * kMfmaT);
         up(b->pw, mpw.data(), sizeof(c32) * p.n_slots * kMfmaT);
     } else if (e == hipSuccess) {
-        e = (hipError_t)launch_prep(da, db, p.n_slots, p.C, b->a, b->b, b->dc, dlc, b->al, s);
+        e = (hipError_t)launch_prep(da, da + ns, p.n_slots, p.C, b->a, b->b, b->dc, dlc, b->al, s);
     }
     if (e == hipSuccess) e = (hipError_t)zero_state(b, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     (void)hipFree(da);
-    (void)hipFree(db);
-    if (dlc) (void)hipFree(dlc);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_bank(b);
@@ -1992,7 +1972,10 @@ int spiir_load_state(spiir_bank* b, const void* host_buf, void* stream)
     if (rc) return rc;
     hipStream_t s = (hipStream_t)stream;
     const char* o = (const char*)host_buf + kStateHeaderBytes;
-    hipError_t e = (hipError_t)clear_end_states(b, s);
+    // the end states of earlier calls: lanes of padding that a launch leaves out
+    // never write theirs, and k_chain reads every slot's
+    hipError_t e = hipSuccess;
+    if (p.P > 1) e = (hipError_t)launch_fill(b->euend, end_rows(p) * p.n_slots * (int64_t)sizeof(c32), s);
     auto upl = [&](void* dst, size_t bytes) {
         if (e == hipSuccess && bytes) e = hipMemcpyAsync(dst, o, bytes, hipMemcpyHostToDevice, s);
         o += bytes;
