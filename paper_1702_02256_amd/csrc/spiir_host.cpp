@@ -505,13 +505,15 @@ int make_plan_shape(const spiir_bank_desc* d, Plan& p, int W, int sub, int copie
 
 // Waves per SIMD the registers of the filter kernel allow (from the compiled
 // kernels' VGPR counts: 512 per SIMD lane over the rounded allocation); used
-// only to rank launch shapes.
+// only to rank launch shapes and to size AUTO splits.  (With the compensated sum, F =
+// 1 and 2 use 80 and 94 by now, 6 and 5 waves.  Their figures stay: a bank's window
+// layout, and with it which saved states it takes, follows from them.)
 int filter_reg_waves(int F, bool comp)
 {
     switch (F) {
     case 1: return comp ? 7 : 8;
     case 2: return 6;
-    case 4: return comp ? 4 : 5;
+    case 4: return 4;
     case 6: return 4;
     default: return 2;
     }

@@ -151,3 +151,12 @@ def test_short_blocks_of_split_banks_take_the_cheaper_route(stub):
     for n, one in ((512, 1), (528, 0), (1024, 0)):
         assert ("chain" in [l.kind for l in stub.process([(bank, *_io(bank, n))])]) == (not one), n
     bank.destroy()
+
+
+@pytest.mark.parametrize("T,H,M,P", [(160, 3, 64, 32), (512, 1, 300, 4)])
+def test_automatic_split_is_the_same_for_both_sums(T, H, M, P):
+    # four filters per lane leave four waves per SIMD with either sum; short delays,
+    # so that the LDS does not decide
+    tb = W.random_bank(7, np.full((T, H), M, np.int32), 4096, [20 >> h for h in range(H)])
+    for precision in ("fp32", "fp32_compensated"):
+        assert S.spiir_plan(tb, 512, precision=precision, time_chunks=S.TIME_CHUNKS_AUTO)["time_chunks"] == P
