@@ -99,7 +99,7 @@ enum {
  *                         lane; fewer when a long delay window would not
  *                         fit the LDS).
  *   device                HIP device ordinal the bank lives on.
- *   time_chunks           P in {0, 1, 2, 4, ..., 64}; 0 or 1: none asked for;
+ *   time_chunks           P in {0, 1, 2, 4, ..., 64}; 0: none asked for, 1: off;
  *                         SPIIR_TIME_CHUNKS_AUTO: the library picks P for
  *                         blocks of max_block samples, splitting while the
  *                         longest workgroup's run of dependent samples, cut
@@ -118,14 +118,14 @@ enum {
  *                         filter pass runs every chunk from its start state.
  *                         Results differ from an unsplit bank's by rounding
  *                         only; where blocks begin changes no bit of them,
- *                         split or not.  The library may run a bank in another
- *                         number of chunks than P, or unsplit, where that is
- *                         faster; spiir_plan reports P.  It splits very small banks
- *                         by itself when neither this, filters_per_lane nor
- *                         waves_per_group is given and max_block is at least
- *                         512 (spiir_plan then still
- *                         reports 1; the footprint and the state include the
- *                         split's arrays).
+ *                         split or not.  spiir_chunks_run gives the number
+ *                         of chunks a bank runs in.  It differs from P where
+ *                         another number, or none, is faster, and is 1 where
+ *                         a1^length exceeds FP32 (|a1| > 1).  With 0, and neither
+ *                         filters_per_lane nor waves_per_group given, the library
+ *                         also splits very small banks for blocks of 512 and
+ *                         more samples (max_block) if every |a1| < 1; their
+ *                         state includes the split's arrays.
  *   window_copies         1 or 2; 0 = chosen by the library.  The filter
  *                         kernel keeps each band's input window in LDS, as
  *                         two copies shifted by one sample (each filter reads
@@ -220,7 +220,8 @@ typedef struct {
 } spiir_request;
 
 /*
- * spiir_footprint — device bytes spiir_create would allocate for `desc`.
+ * spiir_footprint — device bytes spiir_create would allocate for `desc` (very
+ * small banks with time_chunks 1 allocate less: the figure is that with 0).
  * Pure host function: no device call, no allocation.  Returns SPIIR_EINVAL for
  * a descriptor spiir_create would reject.  Used for admission by HBM footprint.
  */
@@ -410,8 +411,8 @@ typedef struct {
     int32_t filters_per_lane; /* F                                             */
     int32_t lds_bytes;        /* dynamic LDS of the filter kernel              */
     int32_t carry_chunk;      /* C                                             */
-    size_t footprint;         /* device bytes spiir_create allocates           */
-    int32_t time_chunks;      /* P (1 = no time split)                         */
+    size_t footprint;         /* device bytes spiir_create allocates (at most) */
+    int32_t time_chunks;      /* P asked for, or AUTO's choice (1 = none)      */
     int32_t window_copies;    /* LDS copies of the input window (1 or 2)       */
     size_t workspace_bytes;   /* device workspace one request needs            */
     int32_t workspace;        /* SPIIR_WORKSPACE_OWN or SPIIR_WORKSPACE_CALLER */
@@ -419,6 +420,10 @@ typedef struct {
 } spiir_plan_info;
 
 int spiir_plan(const spiir_bank_desc* desc, spiir_plan_info* info);
+
+/* Time chunks that a block of max_block samples of the bank is cut in (1: it runs
+ * whole).  Pure host function, errors as spiir_plan. */
+int spiir_chunks_run(const spiir_bank_desc* desc, int32_t* chunks);
 
 /* The same summary for a created bank (the plan spiir_create made, without
  * planning again).  SPIIR_EINVAL for NULL arguments. */

@@ -900,6 +900,7 @@ int make_plan(const spiir_bank_desc* d, Plan& p)
             if (P > 1) set_run(p, P);
             // (a bank that did not ask for it is only split where every filter decays)
             if (p.P > 1 && chunk_growth(d, p) >= 0.0) set_run(p, 1);
+            if (d->time_chunks == 1) set_chunks(p, 1);  // off; the footprint stays that of the default
         }
         return rc;
     }
@@ -1475,6 +1476,20 @@ int spiir_bank_plan(const spiir_bank* bank, spiir_plan_info* info)
     if (!bank || !info) return SPIIR_EINVAL;
     fill_plan_info(bank->plan, info);
     return SPIIR_OK;
+}
+
+int spiir_chunks_run(const spiir_bank_desc* desc, int32_t* chunks)
+{
+    if (!chunks) return SPIIR_EINVAL;
+    Plan p;
+    int rc;
+    try {
+        rc = make_plan(desc, p);
+    } catch (const std::bad_alloc&) {
+        return SPIIR_ENOMEM;
+    }
+    if (rc == SPIIR_OK) *chunks = p.P;
+    return rc;
 }
 
 int spiir_footprint(const spiir_bank_desc* desc, size_t* bytes)

@@ -141,6 +141,7 @@ def load_library():
         "spiir_strerror": (C.c_char_p, [C.c_int]),
         "spiir_samples_done": (C.c_int, [vp, C.POINTER(C.c_int64)]),
         "spiir_plan": (C.c_int, [C.POINTER(BankDesc), C.POINTER(PlanInfo)]),
+        "spiir_chunks_run": (C.c_int, [C.POINTER(BankDesc), C.POINTER(C.c_int32)]),
         "spiir_bank_plan": (C.c_int, [vp, C.POINTER(PlanInfo)]),
         "spiir_profile_enable": (C.c_int, [C.c_int]),
         "spiir_profile_read": (C.c_int, [C.POINTER(ProfileData)]),
@@ -239,6 +240,13 @@ def spiir_plan(tables, max_block, **kw) -> dict:
     info = PlanInfo()
     _check(load_library().spiir_plan(C.byref(h.desc), C.byref(info)), "spiir_plan")
     return {k: getattr(info, k) for k, _ in PlanInfo._fields_}
+
+
+def spiir_chunks_run(tables, max_block, **kw) -> int:
+    h = _DescHolder(tables, max_block, **kw)
+    out = C.c_int32()
+    _check(load_library().spiir_chunks_run(C.byref(h.desc), C.byref(out)), "spiir_chunks_run")
+    return int(out.value)
 
 
 def spiir_footprint(tables, max_block, **kw) -> int:
