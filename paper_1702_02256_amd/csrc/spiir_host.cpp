@@ -34,6 +34,7 @@ constexpr int kXcapMax = 24576;     // LDS window, floats
 constexpr int kMaxLds = 160 * 1024;
 constexpr int kComputeUnits = 256;  // MI355X
 constexpr int kDualSamples = 256;   // blocks of a bank split in time that run in one launch
+constexpr int kDirectGroups = 340;  // most workgroups of a single-rate call that stage for themselves
 constexpr uint32_t kStateMagic = 0x53504952u;  // "SPIR"
 constexpr uint32_t kStateVersion = 3;  // 3: 128-byte header with the layout fingerprint
 constexpr uint32_t kStateVersionSplit = 4;  // 4: and at the end the carried state of a time split
@@ -1258,11 +1259,16 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         for (int k = 0; k < A.nreq; ++k) {
             const Plan& p = req[rmap[k]].bank->plan;
             ReqArg& ra = A.req[k];
-            // a single-rate bank needs neither the cascade nor, where every
-            // template is one piece and z is wanted, the upsample-and-add pass
-            ra.direct = p.H > 1 || p.engine != SPIIR_ENGINE_VALU || p.n_groups == 0 ? 0
-                        : ra.nchunk > 1                                              ? kDirectSplit
-                                                                                    : kDirect;
+            // A single-rate bank needs neither the cascade nor, where every template
+            // is one piece and z is wanted, the upsample-and-add pass.  Without the
+            // staging launch every workgroup counts itself on one word: 9 ns each
+            // against 3 us.  Staged / not, us, 64 and 1024 samples, groups of 128
+            // lanes: 128 of them 20 / 17, 71 / 68; 340 25 / 22, 99 / 99; 512 24 / 24,
+            // 99 / 101; 680 25 / 26, 125 / 129; 1360 28 / 40, 211 / 222 (of 256
+            // lanes 340 24 / 24, 151 / 152, 680 27 / 30, 190 / 194).
+            const bool single = p.H == 1 && p.engine == SPIIR_ENGINE_VALU && p.n_groups > 0;
+            ra.direct = !single ? 0 : ra.nchunk > 1 ? kDirectSplit : p.n_groups <= kDirectGroups ? kDirect : 0;
+            ra.z_direct = single && ra.z && !ra.peaks;
             ra.nblocks = p.n_groups;
             need_stage |= !ra.direct;
         }
@@ -1282,7 +1288,7 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
         for (int k = 0; k < A.nreq; ++k) {
             const Plan& p = req[rmap[k]].bank->plan;
             ReqArg& ra = A.req[k];
-            ra.z_direct = ra.direct && ra.z && !ra.peaks && !overwrites_input(k);
+            ra.z_direct = ra.z_direct && !overwrites_input(k);
             ra.T = ra.z_direct && p.whole_templates ? 0 : p.T;
         }
         // filter workgroups of one shape: band-major across requests (longest

@@ -139,8 +139,8 @@ struct BankDev {
     const c32* pw;
 };
 
-// No staging launch (single-rate banks): the filter kernel reads x itself, or
-// for a bank split in time its end-state pass does.
+// No staging launch (single-rate banks of few workgroups): the filter kernel reads
+// x itself, or for a bank split in time its end-state pass does.
 constexpr int kDirect = 1, kDirectSplit = 2;
 
 struct ReqArg {
@@ -157,7 +157,7 @@ struct ReqArg {
     int32_t nchunk;      // 1, or most time chunks of a band (split in time)
     int32_t dual;        // split in time, but a short block: one workgroup runs its chunks in turn
     int32_t direct;      // who stages the block: 0, kDirect or kDirectSplit
-    int32_t z_direct;    // it also writes z for templates that are one piece
+    int32_t z_direct;    // the filter kernel also writes z for templates that are one piece
     int32_t nblocks;     // workgroups of the request in the filter launch
     int32_t T;           // its templates in the upsample-and-add launch (0: none needed)
 };

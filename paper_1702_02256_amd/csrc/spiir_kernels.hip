@@ -59,7 +59,7 @@ typedef float f32x2_t __attribute__((ext_vector_type(2)));
 // loop, and there it would also wait for the stores, a microsecond each time.
 __device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
-// Requests that need no staging launch (single-rate banks):
+// Requests that need no staging launch (single-rate banks of few workgroups):
 // the filter kernel reads the block's new samples from x itself, its first
 // workgroup appends them to the band-0 ring, and the workgroup that is the last
 // to have read the device clock advances it.  The ring slots of the new samples

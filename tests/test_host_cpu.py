@@ -160,3 +160,14 @@ def test_automatic_split_is_the_same_for_both_sums(T, H, M, P):
     tb = W.random_bank(7, np.full((T, H), M, np.int32), 4096, [20 >> h for h in range(H)])
     for precision in ("fp32", "fp32_compensated"):
         assert S.spiir_plan(tb, 512, precision=precision, time_chunks=S.TIME_CHUNKS_AUTO)["time_chunks"] == P
+
+
+@pytest.mark.parametrize("groups,direct", [(340, 1), (341, 0)])
+def test_many_workgroups_are_staged(stub, groups, direct):
+    bank = stub.bank(_tables(groups, M=256), 512, filters_per_lane=4, waves_per_group=1)
+    assert bank.plan["n_groups"] == groups
+    launches = stub.process([(bank, *_io(bank, 512))])
+    assert [l.kind for l in launches] == ([] if direct else ["stage"]) + [launches[-1].kind]
+    r = launches[-1].req[0]
+    assert (r.direct, r.z_direct, r.T) == (direct, 1, 0)
+    bank.destroy()
