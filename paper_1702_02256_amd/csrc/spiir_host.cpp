@@ -1136,11 +1136,15 @@ const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 // X = 2: 833 workgroups (700 templates, 7 bands) 53 / 64, 61 / 68, 93 / 90; 609 (512
 // templates) 51 / 53, 59 / 58, 91 / 74; 364 (1024 templates, 3 bands) 48 / 43, 57 / 48,
 // 93 / 72; 208 (700 single-rate templates) 41 / 36, 49 / 41, 82 / 63.
-int pipe_threads(int F, int lanes, int longest, double g, int64_t groups)
+// With the compensated sum X = 4 leaves a compute unit one group of 128 lanes at a
+// time (135 registers), so there more than one long group per compute unit is many:
+// 341 single-rate groups, 64, 128, 256, 512 samples 29 / 35, 36 / 42, 54 / 59, 93 / 93,
+// where 254 take 27 / 24, 33 / 27, 48 / 36, 81 / 53.
+int pipe_threads(int F, bool comp, int lanes, int longest, double g, int64_t groups)
 {
     if (F != 4 || 2 * lanes > kPipeThreads || g > 2.0) return 0;
     const int x = g > 1.0 ? 1 : 4 * lanes <= kPipeThreads ? 4 : 2;
-    const bool many = groups > 2 * kComputeUnits;
+    const bool many = groups > 2 * kComputeUnits || (comp && x == 4 && lanes > 64 && g * 256.0 > lanes);
     return longest >= (x == 1 || many ? 32 : x == 2 ? 8 : 4) * kTile ? x : 0;
 }
 
@@ -1226,7 +1230,8 @@ hipError_t enqueue_batch(int32_t n_req, const spiir_request* req, hipStream_t s,
             const double g = (double)work / longest * lanes / (256.0 * kComputeUnits);
             if (lanes_out) *lanes_out = lanes;
             if (fill) *fill = g;
-            return pipe_threads(sh.F, lanes, dual ? std::max(longest, 8 * kTile) : longest, g, dual ? 0 : groups);
+            const bool comp = sh.prec == SPIIR_FP32_COMPENSATED && !dual;
+            return pipe_threads(sh.F, comp, lanes, dual ? std::max(longest, 8 * kTile) : longest, g, dual ? 0 : groups);
         };
         // A short block of a bank split in time runs in one launch, its chunks in
         // turn in one workgroup that carries both runs, where the pipelined kernel

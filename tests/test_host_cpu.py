@@ -171,3 +171,14 @@ def test_many_workgroups_are_staged(stub, groups, direct):
     r = launches[-1].req[0]
     assert (r.direct, r.z_direct, r.T) == (direct, 1, 0)
     bank.destroy()
+
+
+@pytest.mark.parametrize("groups,n,kind", [(256, 256, "pipe"), (257, 256, "filter"), (257, 512, "pipe")])
+def test_short_runs_of_compensated_small_groups(stub, groups, n, kind):
+    # four threads per lane and the compensated sum: one group of 128 lanes per compute unit
+    tb = _tables(groups, M=512)
+    for precision, want in (("fp32_compensated", kind), ("fp32", "pipe")):
+        bank = stub.bank(tb, 512, filters_per_lane=4, waves_per_group=2, precision=precision)
+        launches = stub.process([(bank, *_io(bank, n))])
+        assert bank.plan["n_groups"] == groups and [l.kind for l in launches] == [want]
+        bank.destroy()
