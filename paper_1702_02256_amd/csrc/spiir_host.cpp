@@ -1137,7 +1137,7 @@ const bool g_fail_enqueue = std::getenv("SPIIR_TEST_FAIL_ENQUEUE") != nullptr;
 // templates) 51 / 53, 59 / 58, 91 / 74; 364 (1024 templates, 3 bands) 48 / 43, 57 / 48,
 // 93 / 72; 208 (700 single-rate templates) 41 / 36, 49 / 41, 82 / 63.
 // With the compensated sum X = 4 leaves a compute unit one group of 128 lanes at a
-// time (135 registers), so there more than one long group per compute unit is many:
+// time (133 registers), so there more than one long group per compute unit is many:
 // 341 single-rate groups, 64, 128, 256, 512 samples 29 / 35, 36 / 42, 54 / 59, 93 / 93,
 // where 254 take 27 / 24, 33 / 27, 48 / 36, 81 / 53.
 int pipe_threads(int F, bool comp, int lanes, int longest, double g, int64_t groups)

@@ -463,7 +463,7 @@ __device__ __forceinline__ void start_state(const Start& st, int64_t g, const c3
 {
     y = gmem(st.y)[g];
     u = gmem(st.u)[g];
-    const c32 v{fmaf(d.x, y.x, -d.y * y.y), fmaf(d.x, y.y, d.y * y.x)};
+    const c32 v{fmaf(d.x, y.x, -(d.y * y.y)), fmaf(d.x, y.y, d.y * y.x)};
     u.x = st.fresh ? (LOCAL ? 0.0f : v.x) : u.x;
     u.y = st.fresh ? (LOCAL ? 0.0f : v.y) : u.y;
     if (LOCAL) {
@@ -629,13 +629,14 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 
             // carry correction after the last sample of an absolute chunk of C
             // samples: add the pending correction, then form the next chunk's
-            // from the corrected state (each value keeps its own registers)
+            // from the corrected state (each value keeps its own registers; the
+            // product is negated, not di, whose negative would be kept in registers)
             if (((kabs + cnt) & cmask) == 0) {
 #pragma unroll
                 for (int f = 0; f < F; ++f) {
                     yr[f] += ur[f];
                     yi[f] += ui[f];
-                    ur[f] = fmaf(dr[f], yr[f], -di[f] * yi[f]);
+                    ur[f] = fmaf(dr[f], yr[f], -(di[f] * yi[f]));
                     ui[f] = fmaf(dr[f], yi[f], di[f] * yr[f]);
                 }
             }
@@ -776,8 +777,8 @@ __global__ void __launch_bounds__(filter_max_threads(F), filter_min_waves(F, COM
 //
 // At most kPipeThreads threads, so that a lane may hold 256 registers: a register
 // spilled in the tile loop would be read back behind the workspace stores, a
-// microsecond.  X = 2 uses up to 186 of them (245 with the zero-start run), X = 4 134
-// (173), X = 1 all and spills 25 (32 with the compensated sum), which are read back
+// microsecond.  X = 2 uses up to 182 of them (244 with the zero-start run), X = 4 133
+// (172), X = 1 all and spills 26 (32 with the compensated sum), which are read back
 // once per window, outside the tile loop.
 // ---------------------------------------------------------------------------
 template <int CTRL>
@@ -840,10 +841,13 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
 {
     constexpr int NF = F / X;
     constexpr int kPairs = kRunLanes / 2;
-    // run sums a level-2 task reads ahead: with one thread per lane eight of them
-    // add spills (1024 multi-rate templates, 4096 and 512 samples 437 and 92 us, six
-    // 429 and 87; the compensated sum 466, 446)
+    // run sums a level-2 task reads ahead, and those that pieces of more runs read
+    // together after that.  With one thread per lane eight ahead add spills: 1024
+    // multi-rate templates, 4096 samples 443 us, six ahead 434 (1400, compensated sum,
+    // 569 and 535).  1012 single-rate templates of 508 filters, eight runs each, 4951
+    // samples, compensated sum: 658, 683 with the last two one by one, 672 together.
     constexpr int kRunAhead = X == 1 ? 6 : 8;
+    constexpr int kRunMore = X == 1 ? 2 : 0;
     using Acc = typename std::conditional<COMP, double, float>::type;
     extern __shared__ float sm[];
     const int bid = blockIdx.x;
@@ -1080,12 +1084,28 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
             if (X == 1) acci += in ? (Acc)v2[i].y : (Acc)0;
         }
         const float* l2r = l2f + (parity ^ 1) * l2size;
-        if (long_run)
-            for (int s = run0 + kRunAhead; s < run1; ++s) {
+        if (long_run) {
+            // (the reads of the first few together)
+            f32x2_t w[kRunMore > 0 ? kRunMore : 1];
+#pragma unroll
+            for (int i = 0; i < kRunMore; ++i) {
+                const float* p = l2r + l2off + 2 * (kRunAhead + i);
+                if (X == 1) w[i] = *reinterpret_cast<const f32x2_t*>(p);
+                else w[i].x = *p;
+                keep_single();
+            }
+#pragma unroll
+            for (int i = 0; i < kRunMore; ++i) {
+                const bool in = run0 + kRunAhead + i < run1;
+                accr += in ? (Acc)w[i].x : (Acc)0;
+                if (X == 1) acci += in ? (Acc)w[i].y : (Acc)0;
+            }
+            for (int s = run0 + kRunAhead + kRunMore; s < run1; ++s) {
                 const float* p = l2r + l2off + 2 * (s - run0);
                 accr += p[0];
                 if (X == 1) acci += p[1];
             }
+        }
         if (t2 < ntask2 && j2 < cnt2) {
             SPIIR_AS_GLOBAL float* zp = zrow + 2 * k2;
             if (X == 1) *reinterpret_cast<SPIIR_AS_GLOBAL f32x2_t*>(zp) = f32x2_t{(float)accr, (float)acci};
@@ -1117,12 +1137,12 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
         for (int f = 0; f < NF; ++f) {
             yr[f] += ur[f];
             yi[f] += ui[f];
-            ur[f] = fmaf(dr[f], yr[f], -di[f] * yi[f]);
+            ur[f] = fmaf(dr[f], yr[f], -(di[f] * yi[f]));
             ui[f] = fmaf(dr[f], yi[f], di[f] * yr[f]);
             if (DUAL) {
                 er[f] += eur[f];
                 ei[f] += eui[f];
-                eur[f] = fmaf(dr[f], er[f], -di[f] * ei[f]);
+                eur[f] = fmaf(dr[f], er[f], -(di[f] * ei[f]));
                 eui[f] = fmaf(dr[f], ei[f], di[f] * er[f]);
             }
         }
@@ -1145,7 +1165,7 @@ __global__ void __launch_bounds__(kPipeThreads) k_filter_pipe(LaunchArgs args)
             if (kend < nh) {
                 yr[f] = st.x;
                 yi[f] = st.y;
-                ur[f] = fmaf(dr[f], yr[f], -di[f] * yi[f]);
+                ur[f] = fmaf(dr[f], yr[f], -(di[f] * yi[f]));
                 ui[f] = fmaf(dr[f], yi[f], di[f] * yr[f]);
             }
         }
