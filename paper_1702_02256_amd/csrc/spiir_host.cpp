@@ -698,15 +698,21 @@ int chunks_run(const Plan& p)
 // Time chunks of a bank that asks for none and leaves the launch shape to the
 // library.  The split adds an end-state pass, about half as much work again, so
 // it is kept to small banks: SPIIR_MAX_BATCH of them make at most one workgroup
-// of 256 lanes per compute unit, as long as their longest.  It pays for long
-// blocks of few banks and costs for short ones and full batches.  Measured near
-// that limit (45 templates, 5 bands, max_block 4096), us per call not split /
-// split, blocks of 64, 256, 1024, 4096 samples: one bank 29 / 33, 45 / 55,
-// 108 / 66, 369 / 90; 16 banks 118 / 125, 132 / 146, 200 / 234, 462 / 553.  Far
-// below it (one template in 7 bands): one bank 27 / 28,
-// 33 / 34, 58 / 49, 171 / 56; 16 banks 96 / 97, 102 / 105, 129 / 124, 243 / 147.
-// Banks for blocks under 512 samples never gain: 12 single-rate templates of 300
-// filters, max_block 256 and 512, 37 / 49 and 57 / 39.
+// of 256 lanes per compute unit, as long as their longest.  Which blocks and
+// batches a bank will meet is not known when it is created, and its chunks cannot
+// change with them (that would change bits), so the line weighs gains against
+// losses.  us per call, whole / split, blocks of 64, 256, 512, 1024, 4096 samples:
+//   45 templates, 5 bands (near the line): one bank 30 / 34, 44 / 55, 64 / 63, 106 / 64,
+//     366 / 87; 4 banks 48 / 51, 60 / 70, 79 / 82, 122 / 101, 384 / 161; 16 banks
+//     105 / 124, 129 / 145, 150 / 176, 196 / 221, 453 / 526
+//   24 templates, 5 bands: one 29 / 33, 44 / 55, 64 / 63, 106 / 64, 364 / 74; 16 banks
+//     102 / 111, 118 / 131, 140 / 161, 181 / 175, 446 / 351
+//   one template, 7 bands: one 26 / 27, 31 / 33, 38 / 44, 56 / 48, 168 / 52; 16 banks
+//     97 / 98, 103 / 106, 111 / 116, 129 / 122, 240 / 143
+// So long blocks gain up to four times, short ones lose up to a quarter, and full
+// batches near the line 13 to 18% at any length: time_chunks = 1 is for them.  Banks
+// for blocks under 512 samples never gain: 12 single-rate templates of 300 filters,
+// max_block 256 and 512, 37 / 49 and 57 / 39.
 int small_bank_chunks(const Plan& p)
 {
     int64_t work = 0, longest = 0;
