@@ -12,6 +12,7 @@
 //     each piece in two fixed-order levels (16-lane runs, then runs), so the
 //     result does not depend on anything outside the bank.
 #pragma once
+#include <cstddef>
 #include <cstdint>
 
 #include "spiir.h"
@@ -138,6 +139,12 @@ struct BankDev {
     const c32* kc;
     const c32* pw;
 };
+
+// the filter kernel reads these as pairs
+static_assert(offsetof(BankDev, ys) == offsetof(BankDev, y) + sizeof(c32*) &&
+                  offsetof(BankDev, ys0) == offsetof(BankDev, y0) + sizeof(c32*) &&
+                  offsetof(BankDev, eu) == offsetof(BankDev, ey) + sizeof(c32*),
+              "neighbouring pointers");
 
 // No staging launch (single-rate banks of few workgroups): the filter kernel reads
 // x itself, or for a bank split in time its end-state pass does.
