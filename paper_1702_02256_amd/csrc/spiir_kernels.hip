@@ -436,7 +436,7 @@ struct Start {
 
 // PAIR: neighbouring pointers by one scalar load from a selected address, which a
 // workgroup of k_filter waits for less (4096 multi-rate templates 1237 -> 1229 us); in
-// the pipelined kernel it costs 1% (64 single-rate templates 265 -> 267).
+// the pipelined kernel it costs 1% (86 single-rate templates 265 -> 267).
 template <bool LOCAL, bool PAIR>
 __device__ __forceinline__ Start start_from(CBankDev* bd, int nchunk, int tc)
 {
